@@ -221,18 +221,21 @@ def kernel_classes(hipib):
     return [
         (H.TIMER_SMOOTH_FINE_POISSON, "k_gs<double,2>",
          "finest-level red or black Gauss-Seidel half-sweep of the Poisson solve, 12 B/cell"),
-        (H.TIMER_SMOOTH_FINE_HELMHOLTZ, "k_gs<double,1,true>",
-         "finest-level over-relaxed red or black half-sweep of the Helmholtz solves, 16 B/cell per component"),
-        (H.TIMER_RESID_RESTRICT, "k_resid_restrict<double>", "finest-level red residual and restriction, 13 B/cell"),
-        (H.TIMER_PROLONG, "k_gs_prolong<double,16>",
-         "first post-smoothing half-sweep with the trilinear coarse-grid correction folded in, 13 B/cell"),
-        (H.TIMER_LEVEL_DOWN, "k_level_down<double>", "first coarse level, down half, 17 B per cell of that level"),
-        (H.TIMER_LEVEL_UP, "k_level_up<double>", "first coarse level, up half, 21 B per cell of that level"),
+        (H.TIMER_SMOOTH_FINE_HELMHOLTZ, "k_march<double,relax>",
+         "two over-relaxed red + black sweeps of the Helmholtz solves' finest level, 24 B/cell per component"),
+        (H.TIMER_RESID_RESTRICT, "k_march<double,down>",
+         "finest-level down half: four half-sweeps, residual and restriction, 13 B/cell (17 from an iterate)"),
+        (H.TIMER_PROLONG, "k_march<double,up>",
+         "finest-level up half without dots: coarse-grid correction and four half-sweeps, 21 B/cell"),
+        (H.TIMER_LEVEL_DOWN, "k_march<double,down> (first coarse level)",
+         "first coarse level, down half, 13 B per cell of that level"),
+        (H.TIMER_LEVEL_UP, "k_march<double,up> (first coarse level)",
+         "first coarse level, up half, 21 B per cell of that level"),
         (H.TIMER_SMALL_VCYCLE, "k_exact_fwd_xy / k_exact_z / k_exact_inv_xy <32,double>",
          "coarsest level (32^3) solved exactly, three plane-parallel passes, 16 B per 32^3 cell each"),
         (H.TIMER_RESID_NORM, "k_resid_norm<false>", "residual norm, 16 B/cell per component"),
-        (H.TIMER_CG_DOTS, "k_gs_dot<double>",
-         "last two post-smoothing half-sweeps of the preconditioner, with r.z and z.q, 16 B/cell"),
+        (H.TIMER_CG_DOTS, "k_march<double,up,dots>",
+         "finest-level up half of the preconditioner, with r.z and z.q, 29 B/cell"),
         (H.TIMER_CG_DIR, "k_cg_dir<double>", "p, q = A z + beta q and p.q, 40 B/cell"),
         (H.TIMER_CG_UPDATE, "k_cg_update",
          "alpha from the p.q partials, x, r updates, ||r||^2 and sum-x partials, 48 B/cell"),

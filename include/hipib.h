@@ -371,25 +371,33 @@ hipib_status hipib_convection_vjp(hipib_ctx* ctx, const double* u, const double*
  * on (FP64; n^3 cells, times the components the launch covers): */
 typedef enum {
     HIPIB_TIMER_OFF = 0,
-    /* red or black Gauss-Seidel half-sweep on the finest level of a Poisson
-     * solve (not the first one from a zero guess): 12 B (read the other
-     * colour's half of x and this colour's half of b, write this colour's x) */
+    /* The passes of V(2,2) (mg_pre = mg_post = 2, n a multiple of 8 and at least
+     * 24) are fused; with other smoothing counts the classes 1 to 4 are the
+     * separate kernels named second.  Class 1 then: red or black Gauss-Seidel
+     * half-sweep on the finest level of a Poisson solve (not the first one from
+     * a zero guess): 12 B (read the other colour's half of x and this colour's
+     * half of b, write this colour's x); not launched with V(2,2) */
     HIPIB_TIMER_SMOOTH_FINE_POISSON = 1,
-    /* over-relaxed red or black half-sweep on the finest level of a Helmholtz
-     * solve (on the iterate): 16 B per cell and component (also reads the
-     * colour's own old x) */
+    /* two over-relaxed red + black sweeps on the finest level of a Helmholtz
+     * solve (on the iterate): 24 B per cell and component (x, b; x).  Separate: one
+     * over-relaxed half-sweep, 16 B */
     HIPIB_TIMER_SMOOTH_FINE_HELMHOLTZ = 2,
-    /* finest-level red residual and its restriction: 13 B (x, red b, coarse b) */
+    /* finest-level down half: four half-sweeps, red residual and its
+     * restriction: 13 B from a zero guess (b; red x, coarse b), 17 B from an
+     * iterate (black x, b; red x, coarse b).  Separate: residual and
+     * restriction, 13 B (x, red b; coarse b) */
     HIPIB_TIMER_RESID_RESTRICT = 3,
-    /* finest-level coarse-grid correction: with at least two post-smoothing
-     * sweeps folded into the first (black) post-smoothing half-sweep, 13 B
-     * (that half-sweep's 12 B and the coarse correction); otherwise the
-     * prolongation added to the red cells, 9 B */
+    /* finest-level up half without the conjugate-gradient dots: coarse-grid
+     * correction and four half-sweeps, 21 B (red x, b, coarse correction; x).
+     * Separate: with at least two post-smoothing sweeps the correction folded
+     * into the first (black) post-smoothing half-sweep, 13 B (that half-sweep's
+     * 12 B and the coarse correction); otherwise the prolongation added to the
+     * red cells, 9 B */
     HIPIB_TIMER_PROLONG = 4,
     /* fused first coarse level, down half (four half-sweeps from zero,
-     * residual, restriction): 17 B per cell of that level */
+     * residual, restriction): 13 B per cell of that level */
     HIPIB_TIMER_LEVEL_DOWN = 5,
-    /* fused first coarse level, up half (prolongation, four half-sweeps): 21 B */
+    /* fused first coarse level, up half (correction, four half-sweeps): 21 B */
     HIPIB_TIMER_LEVEL_UP = 6,
     /* the coarsest level: its exact solve (one workgroup per component at
      * most 16^3; three plane-parallel passes at 24^3 and 32^3), or with
@@ -398,9 +406,10 @@ typedef enum {
     HIPIB_TIMER_SMALL_VCYCLE = 7,
     /* residual norm of the finest level: 16 B per cell and component */
     HIPIB_TIMER_RESID_NORM = 8,
-    /* conjugate-gradient passes: r.z and z.q (the preconditioner's last two
-     * finest-level half-sweeps, which sum them: 16 B per cell in FP64; where
-     * the finest level is the exactly solved one, a separate 24 B pass);
+    /* conjugate-gradient passes: r.z and z.q (summed by the preconditioner's
+     * finest-level up half, 29 B per cell in FP64; with separate kernels by its
+     * last two half-sweeps, 16 B; where the finest level is the exactly solved
+     * one, in a separate 24 B pass);
      * p, q = A z + beta q and p.q, 40 B; x, r updates and ||r||^2, 48 B */
     HIPIB_TIMER_CG_DOTS = 9,
     HIPIB_TIMER_CG_DIR = 10,

@@ -314,7 +314,7 @@ hipib_status hipib_create(const hipib_config* cfg, void* stream, hipib_ctx** out
         alloc_bytes(&ctx->lv[l].x, 3 * (size_t)ctx->lv[l].n3 * esz);
         alloc_bytes(&ctx->lv[l].b, 3 * (size_t)ctx->lv[l].n3 * esz);
     }
-    // pre-smoothing arrays of the levels run as fused down/up halves
+    // pre-smoothing arrays of the levels run as fused passes
     for (int l = 1; l < ctx->small_start; ++l)
         if (ctx->lv[l].n % 8 == 0) alloc_bytes(&ctx->lv[l].x2, 3 * (size_t)ctx->lv[l].n3 * esz);
     alloc_bytes(&ctx->r0, 3 * (size_t)ctx->n3 * esz);

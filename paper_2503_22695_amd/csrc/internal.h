@@ -53,7 +53,13 @@ struct Level {
     int64_t n3 = 0;
     void* x = nullptr;     // [3][n3] packed, l >= 1, element type of the V-cycle
     void* b = nullptr;
-    void* x2 = nullptr;    // [3][n3] x after pre-smoothing (levels run as fused halves)
+    void* x2 = nullptr;    // [3][n3] red cells of x after pre-smoothing (levels run as fused passes)
+};
+
+// Box of a fused smoothing pass: a workgroup owns XO packed columns x JO rows x ZO
+// planes; W = XO + 2 HX columns a row with the halo (HX = 0: the whole row)
+struct MarchBox {
+    int W, XO, HX, JO, ZO, ntx, nty, ntz, threads, lds;
 };
 
 struct StepRecord {
@@ -92,7 +98,8 @@ struct hipib_ctx {
     double* coarse_tab = nullptr;
     float* coarse_tab32 = nullptr;
     hipib::Level lv[hipib::kMaxLevels];
-    void* r0 = nullptr;     // [3][n3] residual scratch of the V-cycle type (any level)
+    hipib::MarchBox march_box[hipib::kMaxLevels][3][6] = {};   // by level, components - 1, pass (XO = 0: not chosen yet)
+    void* r0 = nullptr;     // [3][n3] finest-level scratch of the V-cycle type: pre-smoothed x, or the residual
     double* xp = nullptr;   // [3][n3] packed FP64 solution of the current solve
     double* sx = nullptr;   // the packed solution array the running solve iterates on (xp or bp)
     double* kv[4] = {nullptr, nullptr, nullptr, nullptr};  // [n3] packed CG vectors r, z, p, q

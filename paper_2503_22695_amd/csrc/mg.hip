@@ -36,24 +36,25 @@
 // linear smoother this is the same cycle as the FP64 one, with the correction
 // rounded to FP32 (iterative refinement with a V-cycle preconditioner).
 //
-// GPU mapping: one bandwidth-bound kernel per fine-level stage (64x4 thread
-// tiles), with the stages that can share a pass fused (the zero-guess pair of
-// half-sweeps, the coarse-grid correction in the first post-smoothing
-// half-sweep, the CG dots in the last two); the first coarse levels run as
-// one down and one up workgroup-blocked launch each; the exact coarsest solve
+// GPU mapping: a level's V(2,2) halves, and the relaxation of a stop level, run
+// as fused passes (mg_march.h: up to four half-sweeps with the restriction, the
+// coarse-grid correction or the CG dots in one launch); other smoothing counts,
+// and levels of at most 16^3 or with n no multiple of 8, run one kernel per
+// half-sweep (64x4 thread tiles) or in one workgroup; the exact coarsest solve
 // is one workgroup per component (at most 16^3) or three plane-parallel
 // launches (24^3, 32^3).  Up to three components (the three velocity
 // lattices) share every launch and stop independently through per-component
 // `active` flags read at block start.  Stop decisions are made on the device;
 // the host enqueues the predicted number of cycles and waits once to read
 // them.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <vector>
 
 #include <hip/hip_ext.h>
 
-#include "internal.h"
+#include "mg_march.h"
 
 namespace hipib {
 namespace {
@@ -1606,270 +1607,6 @@ k_small_vcycle(T* __restrict__ xg, const T* __restrict__ bg, int64_t cs, SmallAr
 }
 
 // ---------------------------------------------------------------------------
-// coarse levels above the single-workgroup ones: one launch per half of the
-// V-cycle on a level.  Used for V(2,2) with a zero guess (always the case
-// below the finest level) on levels with n a multiple of 8.
-//
-// A workgroup owns an 8^3 block of the level (a 4^3 block of the next one)
-// and recomputes in LDS every cell its result depends on, with the arithmetic
-// of the separate kernels in the same order:
-//   k_level_down: red (from x = 0), black, red, black half-sweeps on boxes
-//     reaching 5, 4, 3, 2 cells beyond the block; red-cell residuals on the
-//     restriction window (1 cell beyond; black residuals are zero after the
-//     black half-sweep); restriction into the next level's b; the smoothed x
-//     of the block is kept for k_level_up.
-//   k_level_up: x_red += prolongated coarse correction on a box reaching 4
-//     cells beyond the block; black, red, black, red half-sweeps on boxes
-//     reaching 3, 2, 1, 0 cells; the block's x is stored.
-// Blocks read neighbours' cells only from arrays no launch of the pair writes,
-// so there is no ordering between workgroups.
-// ---------------------------------------------------------------------------
-
-constexpr int KB = 8;                                 // owned cells per axis
-constexpr int KDH = 5, KUH = 4;                       // halos of the down / up kernels
-constexpr int KDE = KB + 2 * KDH, KUE = KB + 2 * KUH; // LDS box sides (18, 16)
-constexpr int KW = KB + 2;                            // restriction window side
-constexpr int KTHREADS = 1024;
-
-template <int E>
-__device__ __forceinline__ int lix(int a, int b, int c) { return a + E * (b + E * c); }
-
-// packed offset inside a component of the cell at unwrapped (gi, gj, gk)
-__device__ __forceinline__ int64_t pkw(int gi, int gj, int gk, int n) {
-    return pk(wrapi(gi, n), wrapi(gj, n), wrapi(gk, n), n);
-}
-
-// Colour-q cells of the box reaching D cells beyond the owned block (local
-// origin: global cell (g0x, g0y, g0z) at LDS index 0, block at HH):
-// x = (b + c * neighbour sum) * inv_diag; zg: neighbours are zero.  Each
-// thread first loads b for all its cells (all loads in flight), then updates.
-template <int E, int HH, int D, typename T>
-__device__ __forceinline__ void box_gs(T* xs, const T* __restrict__ bg, int n, int g0x, int g0y,
-                                       int g0z, int q, T c, T inv_diag, bool zg) {
-    constexpr int lo = HH - D, S = KB + 2 * D, S2 = S / 2;
-    constexpr int cnt = S2 * S * S, R = (cnt + KTHREADS - 1) / KTHREADS;
-    T bv[R];
-    int oo[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int u = threadIdx.x + r * KTHREADS;
-        oo[r] = -1;
-        if (u < cnt) {
-            const int ah = u % S2, rest = u / S2;
-            const int lb = lo + rest % S, lc = lo + rest / S;
-            const int la = lo + 2 * ah + ((q + g0x + lo + g0y + lb + g0z + lc) & 1);
-            oo[r] = lix<E>(la, lb, lc);
-            bv[r] = bg[pkw(g0x + la, g0y + lb, g0z + lc, n)];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int o = oo[r];
-        if (o >= 0) {
-            T sum = T(0);
-            if (!zg)
-                sum = xs[o + 1] + xs[o - 1] + xs[o + E] + xs[o - E] + xs[o + E * E] + xs[o - E * E];
-            xs[o] = (bv[r] + c * sum) * inv_diag;
-        }
-    }
-}
-
-__device__ __forceinline__ void level_block(int n, int& comp, int& i0, int& j0, int& k0) {
-    const int nb = n / KB, nb3 = nb * nb * nb;
-    comp = blockIdx.x / nb3;
-    const int r = blockIdx.x - comp * nb3;
-    i0 = KB * (r % nb);
-    j0 = KB * ((r / nb) % nb);
-    k0 = KB * (r / (nb * nb));
-}
-
-template <typename T>
-__global__ void __launch_bounds__(KTHREADS)
-k_level_down(const T* __restrict__ b, T* __restrict__ xpre, int n, int64_t cs, T* __restrict__ bc,
-             int64_t ccs, T sigma, T c, T inv_diag, const int32_t* __restrict__ active) {
-    __shared__ T xs[KDE * KDE * KDE];
-    __shared__ T rw[KW * KW * KW];
-    int comp, i0, j0, k0;
-    level_block(n, comp, i0, j0, k0);
-    if (!active[comp]) return;
-    const int g0x = i0 - KDH, g0y = j0 - KDH, g0z = k0 - KDH;
-    const T* bcp = b + comp * cs;
-    constexpr int CW = KW * KW * KW;
-    for (int u = threadIdx.x; u < CW; u += KTHREADS) rw[u] = T(0);   // black entries stay zero
-    // Each thread owns up to RR red cells of the box reaching 5 cells beyond the
-    // block and up to RK black cells of the one reaching 4 (the cells of the
-    // first half-sweep of each colour, numbered as in box_gs); their b is
-    // loaded once, and each later half-sweep updates the owned cells inside its
-    // smaller box (distance from the block: the largest per-axis overhang).
-    constexpr int S5 = KB + 10, CR = (S5 / 2) * S5 * S5, RR = (CR + KTHREADS - 1) / KTHREADS;
-    constexpr int S4 = KB + 8, CK = (S4 / 2) * S4 * S4, RK = (CK + KTHREADS - 1) / KTHREADS;
-    auto dist = [](int la, int lb, int lc) {
-        const int dx = max(max(KDH - la, la - (KDH + KB - 1)), 0);
-        const int dy = max(max(KDH - lb, lb - (KDH + KB - 1)), 0);
-        const int dz = max(max(KDH - lc, lc - (KDH + KB - 1)), 0);
-        return max(dx, max(dy, dz));
-    };
-    T br[RR], bk[RK];
-    int orr[RR], ork[RK], dr[RR], dk[RK], wr[RR];
-#pragma unroll
-    for (int r = 0; r < RR; ++r) {
-        const int u = threadIdx.x + r * KTHREADS;
-        orr[r] = -1;
-        if (u < CR) {
-            const int lo = KDH - 5, ah = u % (S5 / 2), rest = u / (S5 / 2);
-            const int lb = lo + rest % S5, lc = lo + rest / S5;
-            const int la = lo + 2 * ah + ((g0x + lo + g0y + lb + g0z + lc) & 1);
-            orr[r] = lix<KDE>(la, lb, lc);
-            dr[r] = dist(la, lb, lc);
-            wr[r] = dr[r] <= 1 ? lix<KW>(la - (KDH - 1), lb - (KDH - 1), lc - (KDH - 1)) : -1;
-            br[r] = bcp[pkw(g0x + la, g0y + lb, g0z + lc, n)];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < RK; ++r) {
-        const int u = threadIdx.x + r * KTHREADS;
-        ork[r] = -1;
-        if (u < CK) {
-            const int lo = KDH - 4, ah = u % (S4 / 2), rest = u / (S4 / 2);
-            const int lb = lo + rest % S4, lc = lo + rest / S4;
-            const int la = lo + 2 * ah + ((1 + g0x + lo + g0y + lb + g0z + lc) & 1);
-            ork[r] = lix<KDE>(la, lb, lc);
-            dk[r] = dist(la, lb, lc);
-            bk[r] = bcp[pkw(g0x + la, g0y + lb, g0z + lc, n)];
-        }
-    }
-    auto nsum = [&](int o) {
-        return xs[o + 1] + xs[o - 1] + xs[o + KDE] + xs[o - KDE] + xs[o + KDE * KDE] + xs[o - KDE * KDE];
-    };
-    // red from x = 0, black, red, black on boxes reaching 5, 4, 3, 2 cells
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-        if (orr[r] >= 0) xs[orr[r]] = (br[r] + c * T(0)) * inv_diag;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RK; ++r)
-        if (ork[r] >= 0) xs[ork[r]] = (bk[r] + c * nsum(ork[r])) * inv_diag;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-        if (orr[r] >= 0 && dr[r] <= 3) xs[orr[r]] = (br[r] + c * nsum(orr[r])) * inv_diag;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RK; ++r)
-        if (ork[r] >= 0 && dk[r] <= 2) xs[ork[r]] = (bk[r] + c * nsum(ork[r])) * inv_diag;
-    __syncthreads();
-    // red residuals on the restriction window (1 cell beyond the block)
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-        if (orr[r] >= 0 && wr[r] >= 0) {
-            const T xo = xs[orr[r]];
-            rw[wr[r]] = br[r] - (sigma * xo - c * (nsum(orr[r]) - T(6) * xo));
-        }
-    // the block's smoothed x
-    T* xp = xpre + comp * cs;
-    for (int u = threadIdx.x; u < KB * KB * KB; u += KTHREADS) {
-        const int a = u % KB, bb = (u / KB) % KB, cc = u / (KB * KB);
-        xp[pk(i0 + a, j0 + bb, k0 + cc, n)] = xs[lix<KDE>(KDH + a, KDH + bb, KDH + cc)];
-    }
-    __syncthreads();
-    constexpr int KC = KB / 2;
-    if (threadIdx.x < KC * KC * KC) {
-        const int ci = threadIdx.x % KC, cj = (threadIdx.x / KC) % KC, ck = threadIdx.x / (KC * KC);
-        const T w[4] = {T(1), T(3), T(3), T(1)};
-        T sum = T(0);
-        for (int cz = 0; cz < 4; ++cz)
-            for (int cy = 0; cy < 4; ++cy)
-                for (int cx = 0; cx < 4; ++cx)
-                    sum += w[cx] * w[cy] * w[cz] / T(512) * rw[lix<KW>(2 * ci + cx, 2 * cj + cy, 2 * ck + cz)];
-        bc[comp * ccs + pk(i0 / 2 + ci, j0 / 2 + cj, k0 / 2 + ck, n / 2)] = sum;
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(KTHREADS)
-k_level_up(const T* __restrict__ b, const T* __restrict__ xpre, const T* __restrict__ xc,
-           T* __restrict__ x, int n, int64_t cs, int64_t ccs, T c, T inv_diag,
-           const int32_t* __restrict__ active) {
-    __shared__ T xs[KUE * KUE * KUE];
-    int comp, i0, j0, k0;
-    level_block(n, comp, i0, j0, k0);
-    if (!active[comp]) return;
-    const int g0x = i0 - KUH, g0y = j0 - KUH, g0z = k0 - KUH;
-    const int nc = n / 2;
-    const T* bcp = b + comp * cs;
-    const T* xpp = xpre + comp * cs;
-    const T* xcc = xc + comp * ccs;
-    // the coarse correction around the block (the 10^3 coarse cells the
-    // trilinear prolongation reaches from the box) in LDS, read once
-    constexpr int KCE = (KUE / 2) + 2;
-    __shared__ T cs_[KCE * KCE * KCE];
-    const int c0x = g0x / 2 - 1, c0y = g0y / 2 - 1, c0z = g0z / 2 - 1;   // (g0 even)
-    for (int u = threadIdx.x; u < KCE * KCE * KCE; u += KTHREADS) {
-        const int a = u % KCE, bb = (u / KCE) % KCE, cc = u / (KCE * KCE);
-        cs_[u] = xcc[pk(wrapi(c0x + a, nc), wrapi(c0y + bb, nc), wrapi(c0z + cc, nc), nc)];
-    }
-    __syncthreads();
-    // red cells of the whole box: smoothed x plus the trilinear correction
-    {
-        constexpr int S = KUE, S2 = S / 2, CNT = S2 * S * S;
-        const T wt[2] = {T(0.75), T(0.25)};
-        constexpr int R = (CNT + KTHREADS - 1) / KTHREADS;
-        T xv[R];
-        int oo[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int u = threadIdx.x + r * KTHREADS;
-            oo[r] = -1;
-            if (u < CNT) {
-                const int ah = u % S2, rest = u / S2;
-                const int lb = rest % S, lc = rest / S;
-                const int la = 2 * ah + ((g0x + g0y + lb + g0z + lc) & 1);
-                xv[r] = xpp[pkw(g0x + la, g0y + lb, g0z + lc, n)];
-                oo[r] = lix<KUE>(la, lb, lc);
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (oo[r] >= 0) {
-                const int u = threadIdx.x + r * KTHREADS;
-                const int ah = u % S2, rest = u / S2;
-                const int lb = rest % S, lc = rest / S;
-                const int la = 2 * ah + ((g0x + g0y + lb + g0z + lc) & 1);
-                // per axis: nearest coarse cell (unwrapped fine index >> 1) and the next
-                const int l3[3] = {g0x + la, g0y + lb, g0z + lc};
-                const int c3[3] = {c0x, c0y, c0z};
-                int base[3][2];
-                for (int d = 0; d < 3; ++d) {
-                    const int I = (l3[d] >> 1) - c3[d];
-                    base[d][0] = I;
-                    base[d][1] = (l3[d] & 1) ? I + 1 : I - 1;
-                }
-                T v = T(0);
-                for (int cz = 0; cz < 2; ++cz)
-                    for (int cy = 0; cy < 2; ++cy)
-                        for (int cx = 0; cx < 2; ++cx)
-                            v += wt[cx] * wt[cy] * wt[cz] * cs_[lix<KCE>(base[0][cx], base[1][cy], base[2][cz])];
-                xs[oo[r]] = xv[r] + v;
-            }
-        }
-    }
-    __syncthreads();
-    box_gs<KUE, KUH, 3>(xs, bcp, n, g0x, g0y, g0z, 1, c, inv_diag, false);
-    __syncthreads();
-    box_gs<KUE, KUH, 2>(xs, bcp, n, g0x, g0y, g0z, 0, c, inv_diag, false);
-    __syncthreads();
-    box_gs<KUE, KUH, 1>(xs, bcp, n, g0x, g0y, g0z, 1, c, inv_diag, false);
-    __syncthreads();
-    box_gs<KUE, KUH, 0>(xs, bcp, n, g0x, g0y, g0z, 0, c, inv_diag, false);
-    __syncthreads();
-    T* xo = x + comp * cs;
-    for (int u = threadIdx.x; u < KB * KB * KB; u += KTHREADS) {
-        const int a = u % KB, bb = (u / KB) % KB, cc = u / (KB * KB);
-        xo[pk(i0 + a, j0 + bb, k0 + cc, n)] = xs[lix<KUE>(KUH + a, KUH + bb, KUH + cc)];
-    }
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 
@@ -2059,13 +1796,95 @@ hipib_status small_vcycle(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const
     return fail(HIPIB_E_INVAL, "no coarse-level kernel for n = %d", n);
 }
 
-// levels run as one k_level_down / k_level_up pair per V-cycle: the levels
-// below the finest and above the single-workgroup ones with n a multiple of
-// 8, for V(2,2) (there the guess is always zero).  On the finest level the
-// blocks' recomputed halos cost more than the launches they save.
-bool level_fused(const hipib_ctx* ctx, int l) {
-    return l >= 1 && l < ctx->small_start && ctx->lv[l].n % KB == 0 && ctx->lv[l].x2 != nullptr &&
-           ctx->cfg.mg_pre == 2 && ctx->cfg.mg_post == 2;
+// Levels whose V(2,2) halves (and the relaxation of a stop level) run as fused
+// passes.  n a multiple of 8 keeps the boxes' corners even, which the
+// restriction and the correction need.
+bool marched(const hipib_ctx* ctx, int n) {
+    return n % 8 == 0 && n >= 24 && ctx->cfg.mg_pre == 2 && ctx->cfg.mg_post == 2;
+}
+
+// Box of a fused pass.  A step of one workgroup takes about 0.05 us and 0.62 us
+// per 1024 resident threads (FP64, measured over boxes of 448 to 1024 threads on
+// 64^3 and 128^3: LDS accesses bound it; half of that in FP32), whatever part of
+// the threads is halo.  The box taken has the least rounds x steps x step time:
+// large ones repeat less halo, small ones fill the 256 CUs (128^3, one
+// component, down half: 32 x 16 x 8 19.7 us, 32 x 8 x 8 27.1, 32 x 16 x 16 24.5).
+// Rows of fewer than 24 columns lose to the model (96^3 down half with a guess,
+// three components: 16 x 14 x 24 46 us, 24 x 16 x 16 32): too little of a cache
+// line is the box's own.
+MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots, int esz) {
+    const int H = n / 2;
+    MarchBox best{};
+    double tbest = 0.0;
+    const int resident = esz == 8 ? 1024 : 2048;   // threads per CU with the registers of a pass
+    for (int XO : {H, 24, 32, 48, 64}) {
+        if (XO > H || XO > 64) continue;
+        const int HX = XO == H ? 0 : halo_x, W = XO + 2 * HX;
+        for (int JO = 4; JO <= 32 && JO <= n; JO += 2) {
+            const int threads = (W * (JO + 2 * halo) + 63) / 64 * 64;
+            const int lds = slots * threads * esz;
+            if (threads > kMarchThreads || lds > 160 * 1024) break;
+            for (int ZO : {4, 8, 12, 16, 24, 32, 48, 64}) {
+                if (ZO > n) break;
+                const int ntx = (H + XO - 1) / XO, nty = (n + JO - 1) / JO, ntz = (n + ZO - 1) / ZO;
+                const int per_cu = (ntx * nty * ntz * ncomp + 255) / 256;
+                const int fit = std::min(resident / threads, 160 * 1024 / lds), r = std::min(per_cu, fit);
+                const int steps = (ZO + 2 * halo + extra + 3) / 4 * 4;
+                const double t = (double)((per_cu + r - 1) / r) * steps * (0.05 + 0.62 * esz / 8 * threads * r / 1024.0);
+                if (best.XO == 0 || t < tbest) {
+                    tbest = t;
+                    best = MarchBox{W, XO, HX, JO, ZO, ntx, nty, ntz, threads, lds};
+                }
+            }
+        }
+    }
+    return best;
+}
+
+// Launches a fused pass; pass: the slot of its box in the context (the boxes
+// depend on the level, the components and the pass only).
+template <int SRC, int NS, bool SOR, int RES, typename T>
+hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A, int ncomp, int64_t* blocks = nullptr) {
+    constexpr int halo = march_halo(NS, RES), halo_x = march_halo_x(SRC, NS, RES), slots = march_slots(SRC, NS, RES), pass = SRC * 2 + (RES == MARCH_RESTRICT);
+    MarchBox& box = ctx->march_box[l][ncomp - 1][pass];
+    if (box.XO == 0) box = march_box(A.n, ncomp, halo, halo_x, march_extra(RES), slots, (int)sizeof(T));
+    if (box.XO == 0) return fail(HIPIB_E_INVAL, "fused pass: no box for n = %d", A.n);
+    A.box = box;
+    A.st = ctx->st;
+    const int64_t nb = (int64_t)A.box.ntx * A.box.nty * A.box.ntz * ncomp;
+    if (blocks) *blocks = nb;
+    A.pstride = nb;
+    return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES>, dim3((unsigned)nb), dim3(A.box.threads),
+                    (size_t)A.box.lds, A);
+}
+
+// (LDS beyond the 64 KB default; the attribute belongs to the kernel)
+template <typename T>
+hipib_status march_attributes(hipib_ctx* ctx) {
+    const void* ks[] = {reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, false, MARCH_RESTRICT>),
+                        reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, false, MARCH_RESTRICT>),
+                        reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_DOTS>),
+                        reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_X>),
+                        reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, true, MARCH_X>),
+                        reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, true, MARCH_X>)};
+    for (const void* k : ks)
+        HIPIB_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    return HIPIB_OK;
+}
+
+template <typename T>
+MarchArgs<T> march_args(const hipib_ctx* ctx, int l, const OpCoef& oc, int64_t cs) {
+    MarchArgs<T> A{};
+    const int n = ctx->lv[l].n;
+    const T h = T(1) / T(n);
+    A.n = n;
+    A.cs = cs;
+    A.ccs = ctx->lv[l + 1].n3;
+    A.c = (T)oc.nu / (h * h);
+    A.sigma = (T)oc.sigma;
+    A.inv_diag = T(1) / ((T)oc.sigma + T(6) * A.c);
+    A.omega = T(1);
+    return A;
 }
 
 template <typename T>
@@ -2100,6 +1919,24 @@ template <typename T>
 hipib_status relax(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoef& oc, int sweeps,
                    bool zero_guess, double omega) {
     const int n = ctx->lv[l].n;
+    if (marched(ctx, n) && (l == 0 ? sweeps == 4 : sweeps == 2 && zero_guess)) {
+        MarchArgs<T> A = march_args<T>(ctx, l, oc, p.cs);
+        A.omega = (T)omega;
+        A.b = p.b;
+        // two sweeps a pass, on the finest level there and back through r0
+        const double cell = sizeof(T) * (double)ctx->lv[l].n3 * ncomp;
+        const int kind = l == 0 ? HIPIB_TIMER_SMOOTH_FINE_HELMHOLTZ : 0;
+        A.x = p.x;
+        A.out = l == 0 ? static_cast<T*>(ctx->r0) : p.x;
+        if (zero_guess)
+            HIPIB_TRY((march<MARCH_ZERO, 3, true, MARCH_X>(ctx, l, 0, 0.0, A, ncomp)));
+        else
+            HIPIB_TRY((march<MARCH_GUESS, 4, true, MARCH_X>(ctx, l, kind, 3.0 * cell, A, ncomp)));
+        if (l > 0) return HIPIB_OK;
+        A.x = static_cast<const T*>(ctx->r0);
+        A.out = p.x;
+        return march<MARCH_GUESS, 4, true, MARCH_X>(ctx, l, kind, 3.0 * cell, A, ncomp);
+    }
     const T h = T(1) / T(n);
     const T c = (T)oc.nu / (h * h);
     const T inv_diag = T(1) / ((T)oc.sigma + T(6) * c);
@@ -2175,22 +2012,37 @@ hipib_status vcycle(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoe
     const int lc = stop_level(ctx, oc);
     if (l == lc) return relax<T>(ctx, l, p, ncomp, oc, stop_sweeps(ctx, lc), zero_guess,
                                  level_omega(n, oc));
-    if (zero_guess && level_fused(ctx, l)) {
-        const T inv_diag = T(1) / ((T)oc.sigma + T(6) * c);
-        const Level& C = ctx->lv[l + 1];
+    if (marched(ctx, n)) {
+        // the pre-smoothed red cells go to a second array: the up half reads
+        // its neighbours' boxes while it writes x
+        MarchArgs<T> A = march_args<T>(ctx, l, oc, p.cs);
+        T* x2 = static_cast<T*>(l == 0 ? ctx->r0 : ctx->lv[l].x2);
         T* xc = level_x<T>(ctx, l + 1);
         T* bc = level_b<T>(ctx, l + 1);
-        T* x2 = static_cast<T*>(ctx->lv[l].x2);
-        const int nb = n / KB;
-        const unsigned blocks = (unsigned)(nb * nb * nb * ncomp);
-        HIPIB_TRY(launch_k(ctx, l == 1 ? HIPIB_TIMER_LEVEL_DOWN : 0, 17.0 / 8.0 * sizeof(T) * (double)ctx->lv[l].n3 * ncomp,
-                           k_level_down<T>, dim3(blocks), dim3(KTHREADS), 0, p.b, x2, n, p.cs, bc, C.n3,
-                           (T)oc.sigma, c, inv_diag, act));
-        HIPIB_TRY(vcycle<T>(ctx, l + 1, LevelPtr<T>{xc, bc, C.n3}, ncomp, oc, true));
-        HIPIB_TRY(launch_k(ctx, l == 1 ? HIPIB_TIMER_LEVEL_UP : 0, 21.0 / 8.0 * sizeof(T) * (double)ctx->lv[l].n3 * ncomp,
-                           k_level_up<T>, dim3(blocks), dim3(KTHREADS), 0, p.b, x2, xc, p.x, n, p.cs, C.n3, c,
-                           inv_diag, act));
-        return HIPIB_OK;
+        const double cell = sizeof(T) * (double)ctx->lv[l].n3 * ncomp;
+        A.x = p.x;
+        A.b = p.b;
+        A.out = x2;
+        A.bc = bc;
+        const int down = l == 0 ? HIPIB_TIMER_RESID_RESTRICT : l == 1 ? HIPIB_TIMER_LEVEL_DOWN : 0;
+        if (zero_guess)
+            HIPIB_TRY((march<MARCH_ZERO, 3, false, MARCH_RESTRICT>(ctx, l, down, 13.0 / 8.0 * cell, A, ncomp)));
+        else
+            HIPIB_TRY((march<MARCH_GUESS, 4, false, MARCH_RESTRICT>(ctx, l, down, 17.0 / 8.0 * cell, A, ncomp)));
+        HIPIB_TRY(vcycle<T>(ctx, l + 1, LevelPtr<T>{xc, bc, ctx->lv[l + 1].n3}, ncomp, oc, true));
+        A.x = x2;
+        A.out = p.x;
+        A.e = xc;
+        if (l == 0 && ctx->cg_dots.q != nullptr && ncomp == 1) {
+            A.rd = ctx->cg_dots.r;
+            A.qd = ctx->cg_dots.q;
+            A.part = ctx->part;
+            const double bytes = (21.0 / 8.0 * sizeof(T) + (sizeof(T) == 4 ? 16.0 : 8.0)) * (double)ctx->n3;
+            return march<MARCH_CORRECT, 4, false, MARCH_DOTS>(ctx, l, HIPIB_TIMER_CG_DOTS, bytes, A, 1,
+                                                              &ctx->cg_dots.parts);
+        }
+        const int up = l == 0 ? HIPIB_TIMER_PROLONG : l == 1 ? HIPIB_TIMER_LEVEL_UP : 0;
+        return march<MARCH_CORRECT, 4, false, MARCH_X>(ctx, l, up, 21.0 / 8.0 * cell, A, ncomp);
     }
     if (zero_guess && pre == 0) HIPIB_TRY(zero_t<T>(ctx, p.x, ncomp * p.cs));
     HIPIB_TRY(smooth<T>(ctx, l, p, ncomp, oc, pre, 0, zero_guess));
@@ -2369,6 +2221,8 @@ hipib_status mg_prepare(hipib_ctx* ctx) {
         {reinterpret_cast<const void*>(&k_coarse_exact<8, float>), exact_lds_words<8>() * 4}};
     for (const SmallKernel& k : ke)
         HIPIB_HIP(hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, k.bytes));
+    HIPIB_TRY(march_attributes<double>(ctx));
+    HIPIB_TRY(march_attributes<float>(ctx));
     if (ctx->cfg.mg_coarse_sweeps == 0) {
         // the coarsest level's real Fourier basis and eigenvalue factors
         const int N = ctx->lv[ctx->exact_level].n;

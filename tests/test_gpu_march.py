@@ -1,0 +1,57 @@
+"""The fused smoothing passes of the multigrid levels against the oracle: full
+rows and tiles in x, rows and planes that the boxes do not divide evenly, one to
+three components, from a zero guess and from an iterate, as stop levels and
+with relaxed coarsest levels.
+
+A fixed number of cycles on random data, so every pass's rounding is compared
+before the iteration contracts it: a cycle repeats the oracle's operations up to
+the order of the neighbour sums, some 1e-16 of x per half-sweep, so 1e-11 of x
+leaves four digits for the correction's condition.
+"""
+import numpy as np
+import pytest
+
+from tests.test_gpu_parity import TOL, assert_close, host, plain_ctx, say, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    torch.cuda.set_device(0)
+    return torch
+
+
+@pytest.fixture(scope="module")
+def hp():
+    from paper_2503_22695_amd import hipib
+    hipib.lib()
+    return hipib
+
+
+# (n, op, components, dt, krylov, coarse_sweeps): Helmholtz stops descending on the
+# first level with 1 / dt >= 0.06 n_l^2
+CASES = [(48, "poisson", 1, 1e-3, 1, 0), (64, "poisson", 3, 1e-3, 0, 0), (96, "poisson", 1, 1e-3, 0, 0),
+         (128, "poisson", 1, 1e-3, 1, 0), (192, "poisson", 1, 1e-3, 1, 0), (32, "poisson", 1, 1e-3, 1, 4),
+         (24, "poisson", 2, 1e-3, 0, 4), (24, "helmholtz", 3, 1e-3, 1, 0), (64, "helmholtz", 2, 1e-3, 1, 0),
+         (128, "helmholtz", 3, 5e-4, 1, 0), (96, "helmholtz", 3, 1e-2, 1, 0), (128, "helmholtz", 1, 5e-3, 1, 0),
+         (48, "helmholtz", 2, 5e-2, 1, 0)]
+
+
+@pytest.mark.parametrize("n,op,ncomp,dt,krylov,sweeps", CASES)
+def test_fused_cycles(torch_dev, hp, ref, n, op, ncomp, dt, krylov, sweeps):
+    say("fused cycles", n, op, ncomp, dt, krylov, sweeps)
+    rng = np.random.default_rng(1000 + n)
+    b = rng.standard_normal((ncomp, n, n, n))
+    b -= b.mean(axis=(1, 2, 3), keepdims=True)
+    x0 = 1e-3 * rng.standard_normal(b.shape)
+    poisson = op == "poisson"
+    ctx = plain_ctx(hp, n, dt=dt, mg_fixed_cycles=2, mg_krylov=krylov, mg_coarse_sweeps=sweeps)
+    xd = to_dev(torch_dev, x0)
+    ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
+    fl = ref.fluid(n, dt=dt, fixed_cycles=2, krylov=krylov if ncomp == 1 else 0, coarse_sweeps=sweeps)
+    for d in range(ncomp):
+        xr, _, _ = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[d], x0[d])
+        assert_close(f"x[{d}]", host(xd)[d], xr, TOL)
