@@ -1236,14 +1236,45 @@ k_coarse_exact(T* __restrict__ xg, const T* __restrict__ bg, int64_t cs, const T
 //   k_exact_z       plane my: transform along z, divide by lambda, inverse
 //                             along z, in place in W
 //   k_exact_inv_xy  plane k:  inverse along y, then x           -> x (packed)
-// Every output of a pass is one thread's N-term sum over a row of LDS; the
-// basis sits in LDS with rows padded to N + 1 values.  W holds N^3 values per
+// Each transform is an N x N x N product on the matrix cores: wavefront
+// (ti, tj) of a workgroup's four forms the 16 x 16 tile (ti, tj) of the result in
+// N / 4 steps of the 16 x 16 x 4 instruction.  Operands come straight from
+// global memory (basis, plane) except the first product's result, which goes
+// through LDS.  (One thread per output, basis and plane in LDS: 6.0 us a pass at
+// 32^3 in FP64, bound by 2 x 32 LDS reads per output; so: 3.5 to 4.6 us, of which
+// the launch and two chained global reads are the larger part.)  Rows and
+// columns beyond N (24 = 16 + 8) are read from clamped positions and not stored.
+// tab holds Q [N][N], s [N] and the transposed Q [N][N].  W holds N^3 values per
 // component.
-constexpr int kPlaneThreads = 1024;
+constexpr int kPlaneThreads = 256;
 
+template <typename T>
+struct Tile {   // a 16 x 16 tile of a product: element r of a lane is (row(lane, r), lane & 15)
+    typedef T vec __attribute__((ext_vector_type(4)));
+    vec v = {T(0), T(0), T(0), T(0)};
+    __device__ __forceinline__ void add(T a, T b);
+    static __device__ __forceinline__ int row(int lane, int r);
+};
+template <>
+__device__ __forceinline__ void Tile<double>::add(double a, double b) {
+    v = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, v, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ void Tile<float>::add(float a, float b) {
+    v = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, v, 0, 0, 0);
+}
+template <>
+__device__ __forceinline__ int Tile<double>::row(int lane, int r) { return (lane >> 4) + 4 * r; }
+template <>
+__device__ __forceinline__ int Tile<float>::row(int lane, int r) { return 4 * (lane >> 4) + r; }
+
+// a lane's share of an operand: element (k, m) of step t, k = 4 t + lane / 16,
+// m = m0 + lane % 16 (clamped), from an array with k the slow index
 template <int N, typename T>
-__device__ __forceinline__ void exact_load_basis(T* Qs, const T* __restrict__ tab) {
-    for (int t = threadIdx.x; t < N * N; t += kPlaneThreads) Qs[(t / N) * (N + 1) + t % N] = tab[t];
+__device__ __forceinline__ void plane_operand(T (&f)[N / 4], const T* __restrict__ p, int ld, int m0, int lane) {
+    const int m = min(m0 + (lane & 15), N - 1);
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) f[t] = p[(4 * t + (lane >> 4)) * ld + m];
 }
 
 template <int N, typename T>
@@ -1251,29 +1282,36 @@ __global__ void __launch_bounds__(kPlaneThreads)
 k_exact_fwd_xy(const T* __restrict__ bg, int64_t cs, const T* __restrict__ tab, T* __restrict__ work,
                const int32_t* __restrict__ active) {
     constexpr int NP = N + 1;
-    __shared__ T Qs[N * NP], P[N * NP], U[N * NP];
+    __shared__ T U[N * NP];
     const int k = blockIdx.x, comp = blockIdx.y;
-    if (!active[comp]) return;
-    exact_load_basis<N>(Qs, tab);
-    for (int t = threadIdx.x; t < N * N; t += kPlaneThreads) {
-        const int i = t % N, j = t / N;
-        P[j * NP + i] = bg[comp * cs + pkc<N>(i, j, k)];
+    const int lane = threadIdx.x & 63, ti = (threadIdx.x >> 7) * 16, tj = ((threadIdx.x >> 6) & 1) * 16;
+    T a[N / 4], qx[N / 4], qy[N / 4];
+    {   // rows j of the plane
+        const int j = min(ti + (lane & 15), N - 1);
+#pragma unroll
+        for (int t = 0; t < N / 4; ++t) a[t] = bg[comp * cs + pkc<N>(4 * t + (lane >> 4), j, k)];
+    }
+    plane_operand<N>(qx, tab, N, tj, lane);
+    plane_operand<N>(qy, tab, N, ti, lane);
+    if (!active[comp]) return;   // uniform
+    Tile<T> u;                   // U[j][mx] = sum_i b[j][i] Q[i][mx]
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) u.add(a[t], qx[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = ti + Tile<T>::row(lane, r), m = tj + (lane & 15);
+        if (j < N && m < N) U[j * NP + m] = u.v[r];
     }
     __syncthreads();
-    const int t = threadIdx.x, a = t % N, r = t / N;
-    const bool on = t < N * N;
-    if (on) {   // U[j][mx] = sum_i Q[i][mx] b[j][i]
-        T acc = T(0);
-#pragma unroll 8
-        for (int i = 0; i < N; ++i) acc += Qs[i * NP + a] * P[r * NP + i];
-        U[r * NP + a] = acc;
-    }
-    __syncthreads();
-    if (on) {   // W[k][my][mx] = sum_j Q[j][my] U[j][mx]
-        T acc = T(0);
-#pragma unroll 8
-        for (int j = 0; j < N; ++j) acc += Qs[j * NP + r] * U[j * NP + a];
-        work[(int64_t)comp * N * N * N + (k * N + r) * N + a] = acc;
+    T b[N / 4];
+    plane_operand<N>(b, U, NP, tj, lane);
+    Tile<T> w;                   // W[k][my][mx] = sum_j Q[j][my] U[j][mx]
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) w.add(qy[t], b[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int my = ti + Tile<T>::row(lane, r), m = tj + (lane & 15);
+        if (my < N && m < N) work[(int64_t)comp * N * N * N + (k * N + my) * N + m] = w.v[r];
     }
 }
 
@@ -1282,32 +1320,39 @@ __global__ void __launch_bounds__(kPlaneThreads)
 k_exact_z(T* __restrict__ work, const T* __restrict__ tab, T sigma, T nu,
           const int32_t* __restrict__ active) {
     constexpr int NP = N + 1;
-    __shared__ T Qs[N * NP], Z[N * NP], V[N * NP];
-    const int my = blockIdx.x, comp = blockIdx.y;
-    if (!active[comp]) return;
+    __shared__ T V[N * NP];
     const T* sv = tab + N * N;
-    T* wc = work + (int64_t)comp * N * N * N;
-    exact_load_basis<N>(Qs, tab);
-    for (int t = threadIdx.x; t < N * N; t += kPlaneThreads) {
-        const int mx = t % N, k = t / N;
-        Z[k * NP + mx] = wc[(k * N + my) * N + mx];
+    const T* QT = sv + N;
+    const int my = blockIdx.x, comp = blockIdx.y;
+    const int lane = threadIdx.x & 63, ti = (threadIdx.x >> 7) * 16, tj = ((threadIdx.x >> 6) & 1) * 16;
+    T* wc = work + (int64_t)comp * N * N * N + my * N;
+    const int m = tj + (lane & 15);
+    T b[N / 4], qf[N / 4], qi[N / 4];
+    plane_operand<N>(b, wc, N * N, tj, lane);
+    plane_operand<N>(qf, tab, N, ti, lane);
+    plane_operand<N>(qi, QT, N, ti, lane);
+    const T lam_xy = sv[min(m, N - 1)] + sv[my];
+    if (!active[comp]) return;   // uniform
+    Tile<T> v;                   // V[mz][mx] = sum_k Q[k][mz] W[k][my][mx] / lambda(mx, my, mz)
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) v.add(qf[t], b[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int mz = ti + Tile<T>::row(lane, r);
+        if (mz < N && m < N) {
+            const T lam = sigma + nu * (lam_xy + sv[mz]);
+            V[mz * NP + m] = lam != T(0) ? v.v[r] / lam : T(0);
+        }
     }
     __syncthreads();
-    const int t = threadIdx.x, a = t % N, r = t / N;
-    const bool on = t < N * N;
-    if (on) {   // V[mz][mx] = sum_k Q[k][mz] Z[k][mx] / lambda(mx, my, mz)
-        T acc = T(0);
-#pragma unroll 8
-        for (int k = 0; k < N; ++k) acc += Qs[k * NP + r] * Z[k * NP + a];
-        const T lam = sigma + nu * (sv[a] + sv[my] + sv[r]);
-        V[r * NP + a] = lam != T(0) ? acc / lam : T(0);
-    }
-    __syncthreads();
-    if (on) {   // W[k][my][mx] = sum_mz Q[k][mz] V[mz][mx]
-        T acc = T(0);
-#pragma unroll 8
-        for (int m = 0; m < N; ++m) acc += Qs[r * NP + m] * V[m * NP + a];
-        wc[(r * N + my) * N + a] = acc;
+    plane_operand<N>(b, V, NP, tj, lane);
+    Tile<T> w;                   // W[k][my][mx] = sum_mz Q[k][mz] V[mz][mx]
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) w.add(qi[t], b[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int k = ti + Tile<T>::row(lane, r);
+        if (k < N && m < N) wc[k * N * N + m] = w.v[r];
     }
 }
 
@@ -1316,27 +1361,33 @@ __global__ void __launch_bounds__(kPlaneThreads)
 k_exact_inv_xy(T* __restrict__ xg, int64_t cs, const T* __restrict__ tab, const T* __restrict__ work,
                const int32_t* __restrict__ active) {
     constexpr int NP = N + 1;
-    __shared__ T Qs[N * NP], P[N * NP], U[N * NP];
+    __shared__ T U[N * NP];
+    const T* QT = tab + N * N + N;
     const int k = blockIdx.x, comp = blockIdx.y;
-    if (!active[comp]) return;
-    const T* wc = work + (int64_t)comp * N * N * N;
-    exact_load_basis<N>(Qs, tab);
-    for (int t = threadIdx.x; t < N * N; t += kPlaneThreads) P[(t / N) * NP + t % N] = wc[k * N * N + t];
-    __syncthreads();
-    const int t = threadIdx.x, a = t % N, r = t / N;
-    const bool on = t < N * N;
-    if (on) {   // U[j][mx] = sum_my Q[j][my] W[k][my][mx]
-        T acc = T(0);
-#pragma unroll 8
-        for (int m = 0; m < N; ++m) acc += Qs[r * NP + m] * P[m * NP + a];
-        U[r * NP + a] = acc;
+    const int lane = threadIdx.x & 63, ti = (threadIdx.x >> 7) * 16, tj = ((threadIdx.x >> 6) & 1) * 16;
+    T b[N / 4], qy[N / 4], qx[N / 4];
+    plane_operand<N>(b, work + (int64_t)comp * N * N * N + k * N * N, N, tj, lane);
+    plane_operand<N>(qy, QT, N, ti, lane);
+    plane_operand<N>(qx, QT, N, tj, lane);
+    if (!active[comp]) return;   // uniform
+    Tile<T> u;                   // U[j][mx] = sum_my Q[j][my] W[k][my][mx], kept as U[mx][j]
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) u.add(qy[t], b[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = ti + Tile<T>::row(lane, r), m = tj + (lane & 15);
+        if (j < N && m < N) U[m * NP + j] = u.v[r];
     }
     __syncthreads();
-    if (on) {   // x[k][j][i] = sum_mx Q[i][mx] U[j][mx]
-        T acc = T(0);
-#pragma unroll 8
-        for (int m = 0; m < N; ++m) acc += Qs[a * NP + m] * U[r * NP + m];
-        xg[comp * cs + pkc<N>(a, r, k)] = acc;
+    T a[N / 4];
+    plane_operand<N>(a, U, NP, ti, lane);
+    Tile<T> x;                   // x[k][j][i] = sum_mx U[j][mx] Q[i][mx]
+#pragma unroll
+    for (int t = 0; t < N / 4; ++t) x.add(a[t], qx[t]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int j = ti + Tile<T>::row(lane, r), i = tj + (lane & 15);
+        if (j < N && i < N) xg[comp * cs + pkc<N>(i, j, k)] = x.v[r];
     }
 }
 
@@ -2229,7 +2280,7 @@ hipib_status mg_prepare(hipib_ctx* ctx) {
         if (N != 32 && N != 24 && N != 16 && N != 12 && N != 8)
             return fail(HIPIB_E_INVAL, "no exact coarse solve for n = %d", N);
         const double pi = 3.14159265358979323846;
-        std::vector<double> tab((size_t)N * N + N);
+        std::vector<double> tab(2 * (size_t)N * N + N);   // Q, s, Q transposed
         for (int j = 0; j < N; ++j)
             for (int m = 0; m < N; ++m) {
                 double q;
@@ -2238,6 +2289,7 @@ hipib_status mg_prepare(hipib_ctx* ctx) {
                 else if (m == N / 2) q = ((j & 1) ? -1.0 : 1.0) / std::sqrt((double)N);
                 else q = std::sqrt(2.0 / N) * std::sin(2.0 * pi * (m - N / 2) * j / N);
                 tab[(size_t)j * N + m] = q;
+                tab[(size_t)N * N + N + (size_t)m * N + j] = q;
             }
         for (int m = 0; m < N; ++m) {
             const int f = m <= N / 2 ? m : m - N / 2;

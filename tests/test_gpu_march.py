@@ -55,3 +55,26 @@ def test_fused_cycles(torch_dev, hp, ref, n, op, ncomp, dt, krylov, sweeps):
     for d in range(ncomp):
         xr, _, _ = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[d], x0[d])
         assert_close(f"x[{d}]", host(xd)[d], xr, TOL)
+
+
+@pytest.mark.parametrize("n,op,ncomp,mixed", [(24, "poisson", 1, 0), (32, "poisson", 1, 0), (24, "helmholtz", 3, 0),
+                                              (32, "helmholtz", 2, 0), (24, "poisson", 1, 1), (32, "poisson", 1, 1)])
+def test_exact_level(torch_dev, hp, ref, n, op, ncomp, mixed):
+    """The exact solve of a 24^3 or 32^3 level (n not and a multiple of the
+    matrix tiles' 16) as the only level: one plain cycle in FP64 returns the
+    solution, three of the FP32 form with FP64 residuals between them do (each
+    leaves some 1e-6 of the error before it)."""
+    say("exact level", n, op, ncomp, mixed)
+    rng = np.random.default_rng(7 * n + ncomp)
+    b = rng.standard_normal((ncomp, n, n, n))
+    b -= b.mean(axis=(1, 2, 3), keepdims=True)
+    poisson, dt = op == "poisson", 10.0       # (Helmholtz: viscous enough not to stop above the exact level)
+    ctx = plain_ctx(hp, n, dt=dt, mg_fixed_cycles=3 if mixed else 1, mg_krylov=0,
+                    precision=hp.MIXED if mixed else hp.FP64)
+    xd = to_dev(torch_dev, np.zeros_like(b))
+    ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
+    for d in range(ncomp):
+        e = 4.0 * n * n * np.sin(np.pi * np.arange(n) / n) ** 2
+        lam = (0.0 if poisson else 1.0 / dt) + (1.0 if poisson else 0.01) * (e[:, None, None] + e[:, None] + e)
+        lam[0, 0, 0] = np.inf if poisson else lam[0, 0, 0]
+        assert_close(f"x[{d}]", host(xd)[d], np.real(np.fft.ifftn(np.fft.fftn(b[d]) / lam)), TOL)
