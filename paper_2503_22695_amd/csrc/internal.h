@@ -93,12 +93,16 @@ struct hipib_ctx {
         const double* q = nullptr;
         int64_t parts = 0;
     } cg_dots;
+    // set by a plain cycle on the iterate: its last fused pass also sums
+    // ||b - A x||^2 (parts: the partials per component it wrote, 0 if none)
+    bool want_norm = false;
+    int64_t norm_sums = 0;
     int exact_level = 0;    // first level with at most 32 cells per side (the exact coarsest level)
     void* coarse_work = nullptr;   // its transform array (24^3 and 32^3), 3 components
     double* coarse_tab = nullptr;
     float* coarse_tab32 = nullptr;
     hipib::Level lv[hipib::kMaxLevels];
-    hipib::MarchBox march_box[hipib::kMaxLevels][3][6] = {};   // by level, components - 1, pass (XO = 0: not chosen yet)
+    hipib::MarchBox march_box[hipib::kMaxLevels][3][12] = {};   // by level, components - 1, pass (XO = 0: not chosen yet)
     void* r0 = nullptr;     // [3][n3] finest-level scratch of the V-cycle type: pre-smoothed x, or the residual
     double* xp = nullptr;   // [3][n3] packed FP64 solution of the current solve
     double* sx = nullptr;   // the packed solution array the running solve iterates on (xp or bp)

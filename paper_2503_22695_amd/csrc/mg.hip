@@ -1896,15 +1896,17 @@ MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots,
 // depend on the level, the components and the pass only).
 template <int SRC, int NS, bool SOR, int RES, typename T>
 hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A, int ncomp, int64_t* blocks = nullptr) {
-    constexpr int halo = march_halo(NS, RES), halo_x = march_halo_x(SRC, NS, RES), slots = march_slots(SRC, NS, RES), pass = SRC * 2 + (RES == MARCH_RESTRICT);
+    constexpr int halo = march_halo(NS, RES), halo_x = march_halo_x(SRC, NS, RES), slots = march_slots(SRC, NS, RES), lead = march_lead(SRC, NS, RES) - halo;
+    constexpr int pass = 4 * SRC + RES;
     MarchBox& box = ctx->march_box[l][ncomp - 1][pass];
-    if (box.XO == 0) box = march_box(A.n, ncomp, halo, halo_x, march_extra(RES), slots, (int)sizeof(T));
+    if (box.XO == 0) box = march_box(A.n, ncomp, halo, halo_x, lead + march_extra(RES), slots, (int)sizeof(T));
     if (box.XO == 0) return fail(HIPIB_E_INVAL, "fused pass: no box for n = %d", A.n);
     A.box = box;
     A.st = ctx->st;
     const int64_t nb = (int64_t)A.box.ntx * A.box.nty * A.box.ntz * ncomp;
     if (blocks) *blocks = nb;
-    A.pstride = nb;
+    A.pstride = RES == MARCH_NORM ? nb / ncomp : nb;
+    if (RES == MARCH_NORM) A.part = ctx->part;
     return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES>, dim3((unsigned)nb), dim3(A.box.threads),
                     (size_t)A.box.lds, A);
 }
@@ -1912,12 +1914,16 @@ hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A
 // (LDS beyond the 64 KB default; the attribute belongs to the kernel)
 template <typename T>
 hipib_status march_attributes(hipib_ctx* ctx) {
-    const void* ks[] = {reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, false, MARCH_RESTRICT>),
-                        reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, false, MARCH_RESTRICT>),
-                        reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_DOTS>),
-                        reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_X>),
-                        reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, true, MARCH_X>),
-                        reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, true, MARCH_X>)};
+    std::vector<const void*> ks = {reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, false, MARCH_RESTRICT>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, false, MARCH_RESTRICT>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_DOTS>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_X>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, true, MARCH_X>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, true, MARCH_X>)};
+    if constexpr (sizeof(T) == 8) {
+        ks.push_back(reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_NORM>));
+        ks.push_back(reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, true, MARCH_NORM>));
+    }
     for (const void* k : ks)
         HIPIB_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     return HIPIB_OK;
@@ -1986,6 +1992,13 @@ hipib_status relax(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoef
         if (l > 0) return HIPIB_OK;
         A.x = static_cast<const T*>(ctx->r0);
         A.out = p.x;
+        if constexpr (sizeof(T) == 8) {
+            if (ctx->want_norm) {
+                HIPIB_TRY((march<MARCH_GUESS, 4, true, MARCH_NORM>(ctx, l, kind, 3.0 * cell, A, ncomp, &ctx->norm_sums)));
+                ctx->norm_sums /= ncomp;
+                return HIPIB_OK;
+            }
+        }
         return march<MARCH_GUESS, 4, true, MARCH_X>(ctx, l, kind, 3.0 * cell, A, ncomp);
     }
     const T h = T(1) / T(n);
@@ -2091,6 +2104,14 @@ hipib_status vcycle(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoe
             const double bytes = (21.0 / 8.0 * sizeof(T) + (sizeof(T) == 4 ? 16.0 : 8.0)) * (double)ctx->n3;
             return march<MARCH_CORRECT, 4, false, MARCH_DOTS>(ctx, l, HIPIB_TIMER_CG_DOTS, bytes, A, 1,
                                                               &ctx->cg_dots.parts);
+        }
+        if constexpr (sizeof(T) == 8) {
+            if (l == 0 && ctx->want_norm) {
+                HIPIB_TRY((march<MARCH_CORRECT, 4, false, MARCH_NORM>(ctx, l, HIPIB_TIMER_PROLONG, 21.0 / 8.0 * cell, A,
+                                                                      ncomp, &ctx->norm_sums)));
+                ctx->norm_sums /= ncomp;
+                return HIPIB_OK;
+            }
         }
         const int up = l == 0 ? HIPIB_TIMER_PROLONG : l == 1 ? HIPIB_TIMER_LEVEL_UP : 0;
         return march<MARCH_CORRECT, 4, false, MARCH_X>(ctx, l, up, 21.0 / 8.0 * cell, A, ncomp);
@@ -2210,7 +2231,12 @@ hipib_status cycle(hipib_ctx* ctx, int ncomp, const OpCoef& oc) {
         k_update<<<dim3(nb, ncomp), 256, 0, ctx->stream>>>(ctx->sx, ctx->e32, ctx->n3, ctx->st);
         HIPIB_HIP(hipGetLastError());
     } else {
-        HIPIB_TRY(vcycle<double>(ctx, 0, LevelPtr<double>{ctx->sx, ctx->bpk, ctx->n3}, ncomp, oc, false));
+        ctx->want_norm = true;
+        ctx->norm_sums = 0;
+        const hipib_status vs = vcycle<double>(ctx, 0, LevelPtr<double>{ctx->sx, ctx->bpk, ctx->n3}, ncomp, oc, false);
+        ctx->want_norm = false;
+        HIPIB_TRY(vs);
+        if (ctx->norm_sums > 0) return finalize(ctx, ctx->norm_sums, ctx->norm_sums, ncomp, FIN_CYCLE_R, 0.0);
     }
     return resid_norm(ctx, ncomp, oc, FIN_CYCLE_R);
 }

@@ -41,7 +41,8 @@ enum MarchSource {
 enum MarchResult {
     MARCH_X = 0,         // both colours of the smoothed x
     MARCH_RESTRICT = 1,  // its red cells and the restricted residual
-    MARCH_DOTS = 2       // both colours, and the partial sums of r.z and z.q
+    MARCH_DOTS = 2,      // both colours, and the partial sums of r.z and z.q
+    MARCH_NORM = 3       // both colours, and the partial sums of ||b - A x||^2
 };
 
 template <typename T>
@@ -56,7 +57,8 @@ struct MarchArgs {
     int64_t cs, ccs;  // component strides of the level and of the next one
     T c, inv_diag, sigma, omega;
     const MGState* st;
-    // MARCH_DOTS: r (mixed mode: the FP64 residual; FP64: b itself) and q
+    // MARCH_DOTS: r (mixed mode: the FP64 residual; FP64: b itself) and q; partial
+    // sums of MARCH_DOTS and MARCH_NORM (pstride apart: r.z and z.q, or the components)
     const double* rd;
     const double* qd;
     double* part;
@@ -68,18 +70,24 @@ constexpr int kMarchThreads = 1024;   // threads of a workgroup at most: 128 reg
 
 // steps beyond the box and its halo: the restriction's two
 constexpr int march_extra(int result) { return result == MARCH_RESTRICT ? 2 : 0; }
-// halo of the source: one cell per half-sweep, and two for the residual and
-// its restriction
-constexpr int march_halo(int ns, int result) { return result == MARCH_RESTRICT ? ns + 2 : ns; }
+// halo of the source: one cell per half-sweep, one for a residual and one for its
+// restriction
+constexpr int march_halo(int ns, int result) {
+    return result == MARCH_RESTRICT ? ns + 2 : result == MARCH_NORM ? ns + 1 : ns;
+}
+// planes before the box at which a pass starts: even where coarse planes go with it
+constexpr int march_lead(int src, int ns, int result) {
+    return src == MARCH_CORRECT ? (march_halo(ns, result) + 1) / 2 * 2 : march_halo(ns, result);
+}
 // the same in packed columns; a corrected cell also needs the next column's row value
 constexpr int march_halo_x(int src, int ns, int result) {
     return (march_halo(ns, result) + 1) / 2 + (src == MARCH_CORRECT ? 1 : 0);
 }
 // LDS values per column: two planes of each stage that a later one reads
-// in-plane, two of the interpolated coarse rows, four of the residuals and their
-// x sums; odd, so that a wavefront's 8-byte accesses spread over all banks
+// in-plane (the last one too where a residual follows), two of the interpolated
+// coarse rows, four of the restricted residuals and their x sums; odd, so that a wavefront's 8-byte accesses spread over all banks
 constexpr int march_slots(int src, int ns, int result) {
-    return 2 * (ns + (result == MARCH_RESTRICT ? 3 : 0) + (src == MARCH_CORRECT ? 1 : 0)) + 1;
+    return 2 * (ns + (result == MARCH_RESTRICT ? 3 : result == MARCH_NORM ? 1 : 0) + (src == MARCH_CORRECT ? 1 : 0)) + 1;
 }
 
 // s_barrier with the LDS writes before it visible to the workgroup; global
@@ -131,7 +139,10 @@ k_march(MarchArgs<T> A) {
     constexpr int PF = kMarchAhead;
     constexpr int DH = march_halo(NS, RES);
     constexpr int q0 = SRC == MARCH_GUESS ? 1 : 0;           // colour of the source
-    constexpr int NB = RES == MARCH_RESTRICT ? NS + 1 : NS;  // stages with a plane pair in LDS
+    constexpr int DZ = march_lead(SRC, NS, RES);
+    constexpr bool RESID = RES == MARCH_RESTRICT || RES == MARCH_NORM;
+    constexpr int NB = RESID ? NS + 1 : NS;                  // stages with a plane pair in LDS
+    constexpr int qr = (q0 + NS - 1) & 1;                    // colour of the residual: not the last one's
     constexpr int SL = march_slots(SRC, NS, RES), EX = 2 * NB;   // (EX: row values or residuals)
     // age in planes at which b of a colour is first used
     constexpr int FR = SRC == MARCH_ZERO ? 0 : (q0 == 1 ? 1 : 2), FB = SRC == MARCH_GUESS ? 2 : 1;
@@ -187,7 +198,7 @@ k_march(MarchArgs<T> A) {
     for (int s = 0; s <= NS; ++s) hv[s][0] = hv[s][1] = T(0);
 #pragma unroll
     for (int a = 0; a < NA; ++a) bh[0][a] = bh[1][a] = T(0);
-    const int zs = k0 - DH, zlast = k0 + zo - 1 + DH;       // planes of the source
+    const int zs = k0 - DZ, zlast = k0 + zo - 1 + DH;       // planes of the source
     // the next planes to read: byte offsets of the source's plane and of the planes
     // of b that its step needs
     struct Plane {
@@ -330,6 +341,11 @@ k_march(MarchArgs<T> A) {
         }
     };
 
+    // ||b - A x||^2 over the box: the residual of the colour relaxed last is
+    // diag (1 - omega) / omega times its last change (none without over-relaxation)
+    double rn = 0.0;
+    const T wl = (T(1) / A.inv_diag) * (T(1) - A.omega) / A.omega;
+
     // A step runs the half-sweeps in three groups: the source and half-sweep 1, then
     // 2 and 3, then the rest.  Inside a group the code is straight-line: all in-plane
     // sums read what the steps before wrote, so the LDS reads are issued together,
@@ -342,13 +358,13 @@ k_march(MarchArgs<T> A) {
     const int r_lo = __builtin_amdgcn_readfirstlane(r_);
     const int r_hi = __builtin_amdgcn_readfirstlane((tid | 63) / W);
     const bool rows1 = r_hi >= 2 && r_lo < R - 2, rows2 = r_hi >= 4 && r_lo < R - 4;
-    const int steps = zo + 2 * DH + march_extra(RES);
+    const int steps = zo + DZ + DH + march_extra(RES);
     for (int z0 = 0; z0 < steps; z0 += PF) {
         const bool group1 = rows1 && z0 >= 4, group2 = rows2 && z0 >= 8;
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
             const int z = zs + z0 + u;
-            constexpr int ZP = DH & 1;       // parity of zs (k0 is even)
+            constexpr int ZP = DZ & 1;       // parity of zs (k0 is even)
             const int zpar = (ZP + u) & 1;
 #pragma unroll
             for (int a = NA - 1; a > 0; --a) {
@@ -402,10 +418,12 @@ k_march(MarchArgs<T> A) {
                     }
                     T rpre = T(0), rside = T(0);
                     const int ppar = (zpar + NS + 1) & 1;         // parity of the residual's plane
-                    if constexpr (RES == MARCH_RESTRICT) {
+                    if constexpr (RESID) {
                         const T* const Lp = L + 2 * NS + ppar;
-                        const T sn = (Lp[ppar ? sO : sE] + kr) + (Lp[up] + Lp[dn]) + mr;
-                        rpre = bh[0][NS + 1] - (A.sigma * xv - A.c * (sn - T(6) * xv));
+                        const T sn = (Lp[((ppar + qr) & 1) ? sO : sE] + kr) + (Lp[up] + Lp[dn]) + mr;
+                        rpre = bh[qr][NS + 1] - (A.sigma * xv - A.c * (sn - T(6) * xv));
+                    }
+                    if constexpr (RES == MARCH_RESTRICT) {
                         rside = L[EX + 1 - ppar + ((1 - ppar) ? sE : sO)];
                         if (coarse && z - NS - 3 >= k0 - 1) restrict_rows(z - NS - 3, ppar);
                     }
@@ -418,17 +436,24 @@ k_march(MarchArgs<T> A) {
                         rown = rpre + A.c * v;
                         L[pos + EX + ppar] = rown;
                     }
+                    if constexpr (RES == MARCH_NORM) {
+                        const int P = z - NS - 1;
+                        const T res = rpre + A.c * v, last = wl * (v - m2);
+                        if (own && P >= k0 && P < k0 + zo) rn += (double)res * (double)res;
+                        if (SOR && own && P + 1 >= k0 && P + 1 < k0 + zo) rn += (double)last * (double)last;
+                    }
                 }
             }
             if constexpr (RES == MARCH_DOTS) read_dots(z + PF, u);
             lds_barrier();
         }
     }
-    if constexpr (RES == MARCH_DOTS) {
+    if constexpr (RES == MARCH_DOTS || RES == MARCH_NORM) {
+        if (RES == MARCH_NORM) da = rn;
         double* const red = reinterpret_cast<double*>(march_lds);   // (the last barrier is behind every read)
         for (int o = 32; o > 0; o >>= 1) {
             da += __shfl_down(da, o, 64);
-            dd += __shfl_down(dd, o, 64);
+            if (RES == MARCH_DOTS) dd += __shfl_down(dd, o, 64);
         }
         const int nw = nt >> 6;
         if ((tid & 63) == 0) {
@@ -442,8 +467,12 @@ k_march(MarchArgs<T> A) {
                 sa += red[w];
                 sd += red[nw + w];
             }
-            A.part[blk] = sa;
-            A.part[A.pstride + blk] = sd;
+            if (RES == MARCH_DOTS) {
+                A.part[blk] = sa;
+                A.part[A.pstride + blk] = sd;
+            } else {
+                A.part[comp * A.pstride + blk % A.pstride] = sa;   // (pstride: boxes per component)
+            }
         }
     }
 }

@@ -50,11 +50,13 @@ def test_fused_cycles(torch_dev, hp, ref, n, op, ncomp, dt, krylov, sweeps):
     poisson = op == "poisson"
     ctx = plain_ctx(hp, n, dt=dt, mg_fixed_cycles=2, mg_krylov=krylov, mg_coarse_sweeps=sweeps)
     xd = to_dev(torch_dev, x0)
-    ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
+    _, rr = ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
     fl = ref.fluid(n, dt=dt, fixed_cycles=2, krylov=krylov if ncomp == 1 else 0, coarse_sweeps=sweeps)
     for d in range(ncomp):
-        xr, _, _ = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[d], x0[d])
+        xr, _, rrr = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[d], x0[d])
         assert_close(f"x[{d}]", host(xd)[d], xr, TOL)
+        # the residual norm that the last pass sums: b - A x rounds to some eps |b|
+        assert abs(rr[d] - rrr) <= 1e-6 * rrr + 1e-13, (rr[d], rrr)
 
 
 @pytest.mark.parametrize("n,op,ncomp,mixed", [(24, "poisson", 1, 0), (32, "poisson", 1, 0), (24, "helmholtz", 3, 0),
