@@ -1860,15 +1860,16 @@ bool marched(const hipib_ctx* ctx, int n) {
 // the threads is halo.  The box taken has the least rounds x steps x step time:
 // large ones repeat less halo, small ones fill the 256 CUs (128^3, one
 // component, down half: 32 x 16 x 8 19.7 us, 32 x 8 x 8 27.1, 32 x 16 x 16 24.5).
-// Rows of fewer than 24 columns lose to the model (96^3 down half with a guess,
-// three components: 16 x 14 x 24 46 us, 24 x 16 x 16 32): too little of a cache
-// line is the box's own.
+// 1 + 4 / XO stands for the cache lines of a row that are only partly used
+// (192^3, three components, up half with the norm: 16 x 28 x 48 174 us,
+// 24 x 20 x 48 157; 256^3, down half from an iterate: 32 x 14 x 64 332,
+// 16 x 32 x 64 305).
 MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots, int esz) {
     const int H = n / 2;
     MarchBox best{};
     double tbest = 0.0;
     const int resident = esz == 8 ? 1024 : 2048;   // threads per CU with the registers of a pass
-    for (int XO : {H, 24, 32, 48, 64}) {
+    for (int XO : {H, 16, 24, 32, 48, 64}) {
         if (XO > H || XO > 64) continue;
         const int HX = XO == H ? 0 : halo_x, W = XO + 2 * HX;
         for (int JO = 4; JO <= 32 && JO <= n; JO += 2) {
@@ -1881,7 +1882,8 @@ MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots,
                 const int per_cu = (ntx * nty * ntz * ncomp + 255) / 256;
                 const int fit = std::min(resident / threads, 160 * 1024 / lds), r = std::min(per_cu, fit);
                 const int steps = (ZO + 2 * halo + extra + 3) / 4 * 4;
-                const double t = (double)((per_cu + r - 1) / r) * steps * (0.05 + 0.62 * esz / 8 * threads * r / 1024.0);
+                const double t = (double)((per_cu + r - 1) / r) * steps * (0.05 + 0.62 * esz / 8 * threads * r / 1024.0) *
+                                 (1.0 + 4.0 / XO);
                 if (best.XO == 0 || t < tbest) {
                     tbest = t;
                     best = MarchBox{W, XO, HX, JO, ZO, ntx, nty, ntz, threads, lds};
@@ -1905,10 +1907,11 @@ hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A
     A.st = ctx->st;
     const int64_t nb = (int64_t)A.box.ntx * A.box.nty * A.box.ntz * ncomp;
     if (blocks) *blocks = nb;
+    A.nboxes = (unsigned)nb;
     A.pstride = RES == MARCH_NORM ? nb / ncomp : nb;
     if (RES == MARCH_NORM) A.part = ctx->part;
-    return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES>, dim3((unsigned)nb), dim3(A.box.threads),
-                    (size_t)A.box.lds, A);
+    return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES>, dim3((unsigned)((nb + 7) / 8 * 8)),
+                    dim3(A.box.threads), (size_t)A.box.lds, A);
 }
 
 // (LDS beyond the 64 KB default; the attribute belongs to the kernel)

@@ -53,6 +53,7 @@ struct MarchArgs {
     const T* e;       // coarse correction (MARCH_CORRECT)
     T* bc;            // coarse right-hand side (MARCH_RESTRICT)
     int n;
+    unsigned nboxes;  // boxes of all components
     MarchBox box;
     int64_t cs, ccs;  // component strides of the level and of the next one
     T c, inv_diag, sigma, omega;
@@ -151,9 +152,10 @@ k_march(MarchArgs<T> A) {
     extern __shared__ unsigned char march_lds[];
     T* const L = reinterpret_cast<T*>(march_lds);
     const int n = A.n, H = n >> 1, W = A.box.W, tid = threadIdx.x, nt = blockDim.x;
-    // each XCD takes a contiguous eighth of the boxes (see xcd_block)
-    unsigned blk = blockIdx.x;
-    if ((gridDim.x & 7u) == 0) blk = (blk & 7u) * (gridDim.x >> 3) + (blk >> 3);
+    // each XCD takes a contiguous eighth of the boxes (see xcd_block; the grid is the
+    // boxes rounded up to a multiple of 8)
+    const unsigned blk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (blk >= A.nboxes) return;             // uniform
     const int tx = blk % A.box.ntx, ty = (blk / A.box.ntx) % A.box.nty, rest = blk / (A.box.ntx * A.box.nty);
     const int tz = rest % A.box.ntz, comp = rest / A.box.ntz;
     if (!A.st->active[comp]) return;  // uniform
