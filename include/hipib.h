@@ -384,8 +384,10 @@ typedef enum {
     HIPIB_TIMER_SMOOTH_FINE_HELMHOLTZ = 2,
     /* finest-level down half: four half-sweeps, red residual and its
      * restriction: 13 B from a zero guess (b; red x, coarse b), 17 B from an
-     * iterate (black x, b; red x, coarse b).  Separate: residual and
-     * restriction, 13 B (x, red b; coarse b) */
+     * iterate (black x, b; red x, coarse b); 29 B where it first takes the
+     * conjugate-gradient step r = r - alpha q of the iteration before (r, q;
+     * r, red x, coarse b).  Separate: residual and restriction, 13 B (x, red
+     * b; coarse b) */
     HIPIB_TIMER_RESID_RESTRICT = 3,
     /* finest-level up half without the conjugate-gradient dots: coarse-grid
      * correction and four half-sweeps, 21 B (red x, b, coarse correction; x).
@@ -410,7 +412,9 @@ typedef enum {
      * finest-level up half, 29 B per cell in FP64; with separate kernels by its
      * last two half-sweeps, 16 B; where the finest level is the exactly solved
      * one, in a separate 24 B pass);
-     * p, q = A z + beta q and p.q, 40 B; x, r updates and ||r||^2, 48 B */
+     * p, q = A z + beta q and p.q, 40 B, or 56 B with the x step of the
+     * iteration before; x, r updates and ||r||^2, 48 B (where the passes of the
+     * next iteration take these steps, after a batch's last iteration only) */
     HIPIB_TIMER_CG_DOTS = 9,
     HIPIB_TIMER_CG_DIR = 10,
     HIPIB_TIMER_CG_UPDATE = 11,

@@ -43,9 +43,11 @@ struct MGState {
     int32_t status;     // HIPIB_OK / HIPIB_E_NOCONV / HIPIB_E_NUMERIC
     int32_t numeric;    // set by the force kernel when J <= 0
     int32_t bad_position;  // set by the node binning for a non-finite or out-of-range position
-    int32_t pad[2];
-    // conjugate gradients (component 0): r.z, step alpha, direction update beta
-    double rz, alpha, beta;
+    int32_t x_pending;     // conjugate gradients stopped with x += alpha p still to do
+    int32_t pad;
+    // conjugate gradients (component 0): r.z of the latest two iterations (by the
+    // parity of their number), step alpha, direction update beta
+    double rz[2], alpha, beta;
 };
 
 struct Level {
@@ -93,6 +95,16 @@ struct hipib_ctx {
         const double* q = nullptr;
         int64_t parts = 0;
     } cg_dots;
+    // set by a conjugate-gradient iteration whose finest-level down half first forms
+    // r = rold - alpha q of the iteration before (rnew: where to)
+    struct CgUpdate {
+        bool on = false;
+        const double* rold = nullptr;
+        double* rnew = nullptr;
+        const double* q = nullptr;
+        const double* pq = nullptr;
+        int npq = 0, slot = 0;   // partials of p.q; slot of r.z
+    } cg_update;
     // set by a plain cycle on the iterate: its last fused pass also sums
     // ||b - A x||^2 (parts: the partials per component it wrote, 0 if none)
     bool want_norm = false;
@@ -107,6 +119,7 @@ struct hipib_ctx {
     double* xp = nullptr;   // [3][n3] packed FP64 solution of the current solve
     double* sx = nullptr;   // the packed solution array the running solve iterates on (xp or bp)
     double* kv[4] = {nullptr, nullptr, nullptr, nullptr};  // [n3] packed CG vectors r, z, p, q
+    double* cg_r = nullptr; // r of the running conjugate gradients (kv[0] or bpk's second component)
     double* bpk = nullptr;  // [3][n3] packed FP64 right-hand side
     float* e32 = nullptr;   // [3][n3] packed FP32 correction (mixed precision)
     float* r32 = nullptr;   // [3][n3] packed FP32 scaled residual (mixed precision)

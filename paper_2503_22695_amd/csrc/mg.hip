@@ -50,6 +50,7 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include <hip/hip_ext.h>
@@ -65,6 +66,7 @@ constexpr int kSmallThreads = 1024;
 enum FinalizeMode {
     FIN_BNORM = 0, FIN_INIT_R = 1, FIN_CYCLE_R = 2, FIN_MEAN = 3, FIN_MEAN_ALL = 4,
     FIN_MEAN_BNORM = 5,  // component 0: mean of b from slot 0 (sum b), ||b - mean|| with slot 1 (sum b^2)
+    FIN_CG_STEP = 7,     // as FIN_CYCLE_R, in an iteration whose x += alpha p is still to do
     FIN_BNORM_INIT_R = 6 // per component: ||b|| from the b^2 partials after ncomp * pstride, then as FIN_INIT_R
 };
 
@@ -801,30 +803,46 @@ k_cg_dots(const double* __restrict__ r, const TZ* __restrict__ z, const double* 
     }
 }
 
-// p = z + beta p and q = A z + beta q (= A p), partial p.q per block; grid and
-// columns as k_resid_norm
-template <typename TZ>
+// p = z + beta p and q = A z + beta q (= A p) with the partial sums of p.q.  Grid
+// and columns as k_resid_norm.  FUSE: x += alpha p with the p of before where xs is
+// not null (the step that the down half of this iteration's preconditioner applied
+// to r), and beta = -alpha (z.q) / (r.z)_old (0 on the first iteration) is formed
+// here from the nd dot partials (r.z, and z.q after dstride), summed by every
+// workgroup in the same order; else k_cg_scalars left it in the state.  The sum
+// costs a barrier behind all of the workgroup's reads, less than the launch where
+// the vectors come from the last-level cache (128^3: 15.6 + 4.4 us -> 17.2) and more
+// from HBM (192^3: 72.9 -> 78.1).  (512 threads looping over several tiles, for
+// fewer p.q partials: 4.2 TB/s instead of 5.4 at 128^3.)
+template <typename TZ, bool FUSE>
 __global__ void __launch_bounds__(TX * TY)
-k_cg_dir(const TZ* __restrict__ z, double* __restrict__ p, double* __restrict__ q, int n,
-         double sigma, double c, const MGState* __restrict__ st, double* __restrict__ part) {
-    __shared__ double red[16];
+k_cg_dir(const TZ* __restrict__ z, double* __restrict__ p, double* __restrict__ q, double* __restrict__ xs, int n,
+         double sigma, double c, MGState* __restrict__ st, const double* __restrict__ dots, int nd, int64_t dstride,
+         int first, int slot, double* __restrict__ part) {
+    __shared__ double red[2][TY];
     const int nkb = (n + KPT - 1) / KPT;
     const uint3 bid = xcd_block();
     const int rem = bid.z, qc = rem / nkb, k0 = (rem - qc * nkb) * KPT;
     if (!st->active[0]) return;  // uniform
-    const double beta = st->beta, zs = sizeof(TZ) == 4 ? st->bn[0] : 1.0;
+    const double zs = sizeof(TZ) == 4 ? st->bn[0] : 1.0, alpha = st->alpha, old = st->rz[1 - slot];
+    const int tid = threadIdx.x + TX * threadIdx.y, lane = tid & 63;
+    double a = 0.0, d = 0.0, beta = FUSE || first ? 0.0 : st->beta;
+    if constexpr (FUSE)
+        for (int t = tid; t < nd; t += TX * TY) {
+            a += dots[t];
+            d += dots[dstride + t];
+        }
     const int H = n >> 1;
     const int ih = bid.x * TX + threadIdx.x, j = bid.y * TY + threadIdx.y;
-    double v = 0.0;
-    if (ih < H && j < n) {
-        const int64_t half3 = (int64_t)H * n * n;
-        const TZ* zq = z + qc * half3;
-        const TZ* zo = z + (1 - qc) * half3;
-        double* pq = p + qc * half3;
-        double* qq = q + qc * half3;
+    const bool in = ih < H && j < n;
+    const int64_t half3 = (int64_t)H * n * n;
+    const TZ* zq = z + qc * half3;
+    const TZ* zo = z + (1 - qc) * half3;
+    double* pq = p + qc * half3;
+    double* qq = q + qc * half3;
+    double col[KPT + 2], side[KPT], yp[KPT], ym[KPT], zv[KPT], pv[KPT], qv[KPT], xv[KPT];
+    if (in) {   // (all reads are in flight while the dots are summed)
         const int jp = wrapi(j + 1, n), jm = wrapi(j - 1, n);
         const int ihp = ih + 1 < H ? ih + 1 : 0, ihm = ih > 0 ? ih - 1 : H - 1;
-        double col[KPT + 2], side[KPT], yp[KPT], ym[KPT], zv[KPT], pv[KPT], qv[KPT];
 #pragma unroll
         for (int r = 0; r < KPT + 2; ++r)
             col[r] = zs * (double)zo[ih + (int64_t)H * ((int64_t)j + (int64_t)n * wrapi(k0 - 1 + r, n))];
@@ -838,10 +856,34 @@ k_cg_dir(const TZ* __restrict__ z, double* __restrict__ p, double* __restrict__ 
                 side[r] = zs * (double)zo[row + (pp ? ihp : ihm)];
                 yp[r] = zs * (double)zo[(int64_t)H * ((int64_t)jp + (int64_t)n * k) + ih];
                 ym[r] = zs * (double)zo[(int64_t)H * ((int64_t)jm + (int64_t)n * k) + ih];
-                pv[r] = beta != 0.0 ? pq[row + ih] : 0.0;
-                qv[r] = beta != 0.0 ? qq[row + ih] : 0.0;
+                pv[r] = first ? 0.0 : pq[row + ih];
+                qv[r] = first ? 0.0 : qq[row + ih];
+                if constexpr (FUSE) xv[r] = xs ? xs[qc * half3 + row + ih] : 0.0;
             }
         }
+    }
+    if constexpr (FUSE) {
+        for (int o = 32; o > 0; o >>= 1) {
+            a += __shfl_down(a, o, 64);
+            d += __shfl_down(d, o, 64);
+        }
+        if (lane == 0) {
+            red[0][tid >> 6] = a;
+            red[1][tid >> 6] = d;
+        }
+        __syncthreads();
+        a = d = 0.0;
+#pragma unroll
+        for (int w = 0; w < TY; ++w) {
+            a += red[0][w];
+            d += red[1][w];
+        }
+        beta = (first || old == 0.0) ? 0.0 : -alpha * d / old;
+        if (tid == 0 && blockIdx.x + blockIdx.y + blockIdx.z == 0) st->rz[slot] = a;
+        __syncthreads();
+    }
+    double v = 0.0;
+    if (in) {
 #pragma unroll
         for (int r = 0; r < KPT; ++r) {
             const int k = k0 + r;
@@ -856,44 +898,50 @@ k_cg_dir(const TZ* __restrict__ z, double* __restrict__ p, double* __restrict__ 
                 const int64_t row = (int64_t)H * ((int64_t)j + (int64_t)n * k);
                 pq[row + ih] = pn;
                 qq[row + ih] = qn;
+                if constexpr (FUSE)
+                    if (xs) xs[qc * half3 + row + ih] = xv[r] + alpha * pv[r];
                 v += pn * qn;
             }
         }
     }
-    const int tid = threadIdx.x + TX * threadIdx.y;
     for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = v;
+    if (lane == 0) red[0][tid >> 6] = v;
     __syncthreads();
     if (tid == 0) {
         double s = 0.0;
-        for (int w = 0; w < (TX * TY) / 64; ++w) s += red[w];
+        for (int w = 0; w < TY; ++w) s += red[0][w];
         part[bid.x + (int64_t)gridDim.x * (bid.y + (int64_t)gridDim.y * rem)] = s;
     }
 }
 
-// alpha = (r.z) / (p.q), p.q summed from the npq partials of k_cg_dir in a
-// fixed order by every block (so all blocks hold the same alpha; block 0 keeps
-// it in the state for the next beta); then x += alpha p, r -= alpha q, partials
-// of ||r||^2 (part[block]) and of sum x (part[gridDim.x + block], for the mean
-// of the converged solution); r32 (mixed) = r / ||b||
+// The end of the enqueued iterations: alpha = (r.z) / (p.q), p.q summed from the
+// npq partials of k_cg_dir in a fixed order by every block (so all blocks hold
+// the same alpha; block 0 keeps it in the state for the next beta); then
+// x += alpha p, r -= alpha q, partials of ||r||^2 (part[block]) and of sum x
+// (part[gridDim.x + block], for the mean of the converged solution); r32 (mixed)
+// = r / ||b||.  Where an iteration before has stopped, only its step of x is due.
 constexpr int kUpdThreads = 512, kUpdMaxBlocks = 512;   // (256 x 1024: 22.1 us at 128^3; 512 x 512: 19.7)
 __global__ void __launch_bounds__(kUpdThreads)
 k_cg_update(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-            const double* __restrict__ q, int64_t n3, MGState* __restrict__ st,
-            float* __restrict__ r32, const double* __restrict__ pq_part, int64_t npq, double* __restrict__ part) {
+            const double* __restrict__ q, int64_t n3, MGState* __restrict__ st, int slot,
+            float* __restrict__ r32, const double* __restrict__ pq_part, int npq, double* __restrict__ part) {
     __shared__ double red[16];
-    if (!st->active[0]) return;  // uniform
-    double a = 0.0;
-    for (int64_t t = threadIdx.x; t < npq; t += kUpdThreads) a += pq_part[t];
-    a = block_sum(a, red);
-    __shared__ double alpha_s;
-    if (threadIdx.x == 0) {
-        alpha_s = a != 0.0 ? st->rz / a : 0.0;
-        if (blockIdx.x == 0) st->alpha = alpha_s;
-    }
-    __syncthreads();
-    const double alpha = alpha_s, inv_bn = r32 ? 1.0 / st->bn[0] : 0.0;
     const int64_t stride = (int64_t)gridDim.x * kUpdThreads;
+    if (!st->active[0]) {  // uniform
+        if (!st->x_pending) return;
+        const double alpha = st->alpha;
+        double sx = 0.0;
+        for (int64_t t = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x; t < n3; t += stride) {
+            const double xn = x[t] + alpha * p[t];
+            x[t] = xn;
+            sx += xn;
+        }
+        sx = block_sum(sx, red);
+        if (threadIdx.x == 0) part[gridDim.x + blockIdx.x] = sx;
+        return;
+    }
+    const double alpha = cg_alpha(pq_part, npq, st->rz[slot], red), inv_bn = r32 ? 1.0 / st->bn[0] : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->alpha = alpha;
     double v = 0.0, sx = 0.0;
     for (int64_t t0 = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x; t0 < n3; t0 += 4 * stride) {
         double xv[4], rv[4], pv[4], qv[4];
@@ -932,7 +980,7 @@ k_cg_update(double* __restrict__ x, double* __restrict__ r, const double* __rest
 // reduce the dot partials (slot 0: r.z, slot 1: z.q) in a fixed order; beta and
 // the new r.z into the state
 __global__ void __launch_bounds__(1024)
-k_cg_scalars(const double* __restrict__ part, int64_t nparts, int64_t pstride, MGState* st) {
+k_cg_scalars(const double* __restrict__ part, int64_t nparts, int64_t pstride, MGState* st, int first, int slot) {
     __shared__ double red[16];
     if (!st->active[0]) return;  // uniform
     double a = 0.0, b = 0.0;
@@ -944,8 +992,9 @@ k_cg_scalars(const double* __restrict__ part, int64_t nparts, int64_t pstride, M
     b = block_sum(b, red);
     if (threadIdx.x == 0) {
         // a = r.z (new), b = z.q with q = A p of the previous iteration
-        st->beta = (st->cycles[0] == 0 || st->rz == 0.0) ? 0.0 : -st->alpha * b / st->rz;
-        st->rz = a;
+        const double old = st->rz[1 - slot];
+        st->beta = (first || old == 0.0) ? 0.0 : -st->alpha * b / old;
+        st->rz[slot] = a;
     }
 }
 
@@ -1025,7 +1074,7 @@ k_finalize(const double* __restrict__ part, int64_t nparts, int64_t pstride, int
         return;
     }
     for (int comp = 0; comp < ncomp; ++comp) {
-        const bool skip = (mode == FIN_CYCLE_R || mode == FIN_MEAN) && !st->active[comp];
+        const bool skip = (mode == FIN_CYCLE_R || mode == FIN_CG_STEP || mode == FIN_MEAN) && !st->active[comp];
         if (skip) continue;  // uniform across the block
         if (mode == FIN_BNORM_INIT_R) {
             double sb = 0.0;
@@ -1086,6 +1135,7 @@ k_finalize(const double* __restrict__ part, int64_t nparts, int64_t pstride, int
                     }
                 }
                 st->active[comp] = act;
+                if (mode == FIN_CG_STEP && !act) st->x_pending = 1;
             }
         }
         __syncthreads();
@@ -1101,6 +1151,7 @@ __global__ void k_state_reset(MGState* st, int ncomp) {
             st->mean[c] = 0.0;
         }
         st->status = HIPIB_OK;
+        st->x_pending = 0;
     }
 }
 
@@ -1748,6 +1799,16 @@ hipib_status finalize(hipib_ctx* ctx, int64_t nparts, int64_t pstride, int ncomp
     return finalize_at(ctx, 0, nparts, pstride, ncomp, mode, inv_count);
 }
 
+// device address of a double of the state (no host access to the state)
+double* state_field(const hipib_ctx* ctx, size_t offset) {
+    return reinterpret_cast<double*>(reinterpret_cast<char*>(ctx->st) + offset);
+}
+
+// partials of conjugate gradients: the dots first (at most twice 2 norm_parts of
+// each), then p.q (norm_parts), then ||r||^2 and sum x
+int64_t cg_pq_offset(int n) { return 4 * norm_parts(n); }
+int64_t cg_norm_offset(int n) { return cg_pq_offset(n) + norm_parts(n); }
+
 template <typename T>
 hipib_status zero_t(hipib_ctx* ctx, T* p, int64_t count) {
     if (count <= 0) return HIPIB_OK;
@@ -1896,8 +1957,10 @@ MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots,
 
 // Launches a fused pass; pass: the slot of its box in the context (the boxes
 // depend on the level, the components and the pass only).
-template <int SRC, int NS, bool SOR, int RES, typename T>
-hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A, int ncomp, int64_t* blocks = nullptr) {
+template <int SRC, int NS, bool SOR, int RES, bool CG = false, typename T>
+hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, const MarchArgs<T>& args, int ncomp,
+                   int64_t* blocks = nullptr, std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A = {}) {
+    static_cast<MarchArgs<T>&>(A) = args;
     constexpr int halo = march_halo(NS, RES), halo_x = march_halo_x(SRC, NS, RES), slots = march_slots(SRC, NS, RES), lead = march_lead(SRC, NS, RES) - halo;
     constexpr int pass = 4 * SRC + RES;
     MarchBox& box = ctx->march_box[l][ncomp - 1][pass];
@@ -1910,7 +1973,7 @@ hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A
     A.nboxes = (unsigned)nb;
     A.pstride = RES == MARCH_NORM ? nb / ncomp : nb;
     if (RES == MARCH_NORM) A.part = ctx->part;
-    return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES>, dim3((unsigned)((nb + 7) / 8 * 8)),
+    return launch_k(ctx, kind, bytes, k_march<T, SRC, NS, SOR, RES, CG>, dim3((unsigned)((nb + 7) / 8 * 8)),
                     dim3(A.box.threads), (size_t)A.box.lds, A);
 }
 
@@ -1918,6 +1981,7 @@ hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, MarchArgs<T> A
 template <typename T>
 hipib_status march_attributes(hipib_ctx* ctx) {
     std::vector<const void*> ks = {reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, false, MARCH_RESTRICT>),
+                                   reinterpret_cast<const void*>(&k_march<T, MARCH_ZERO, 3, false, MARCH_RESTRICT, true>),
                                    reinterpret_cast<const void*>(&k_march<T, MARCH_GUESS, 4, false, MARCH_RESTRICT>),
                                    reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_DOTS>),
                                    reinterpret_cast<const void*>(&k_march<T, MARCH_CORRECT, 4, false, MARCH_X>),
@@ -2092,7 +2156,25 @@ hipib_status vcycle(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoe
         A.out = x2;
         A.bc = bc;
         const int down = l == 0 ? HIPIB_TIMER_RESID_RESTRICT : l == 1 ? HIPIB_TIMER_LEVEL_DOWN : 0;
-        if (zero_guess)
+        if (zero_guess && l == 0 && ctx->cg_update.on) {
+            // first r = rold - alpha q of the iteration before, and its stop test
+            const hipib_ctx::CgUpdate& g = ctx->cg_update;
+            int64_t boxes = 0;
+            MarchCgArgs<T> C{};
+            C.rold = g.rold;
+            C.rnew = g.rnew;
+            C.b32 = ctx->r32;
+            C.pq = g.pq;
+            C.npq = g.npq;
+            C.rz = state_field(ctx, offsetof(MGState, rz)) + g.slot;
+            C.alpha = state_field(ctx, offsetof(MGState, alpha));
+            A.qd = g.q;
+            A.part = ctx->part + cg_norm_offset(n);
+            HIPIB_TRY((march<MARCH_ZERO, 3, false, MARCH_RESTRICT, true>(
+                ctx, l, down, (24.0 + (sizeof(T) == 4 ? 4.0 : 0.0) + 5.0 / 8.0 * sizeof(T)) * (double)ctx->n3, A, 1, &boxes, C)));
+            HIPIB_TRY(finalize_at(ctx, cg_norm_offset(n), boxes, boxes, 1, FIN_CG_STEP, 0.0));
+            if constexpr (sizeof(T) == 8) A.b = g.rnew;
+        } else if (zero_guess)
             HIPIB_TRY((march<MARCH_ZERO, 3, false, MARCH_RESTRICT>(ctx, l, down, 13.0 / 8.0 * cell, A, ncomp)));
         else
             HIPIB_TRY((march<MARCH_GUESS, 4, false, MARCH_RESTRICT>(ctx, l, down, 17.0 / 8.0 * cell, A, ncomp)));
@@ -2177,24 +2259,48 @@ hipib_status resid_norm(hipib_ctx* ctx, int ncomp, const OpCoef& oc, int mode,
     return finalize(ctx, np, np, ncomp, mode, 0.0);
 }
 
-// one preconditioned conjugate-gradient iteration of the Poisson solve
-hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc) {
+// Whether an iteration's step of r is left to the down half of the next one and
+// its step of x to the next k_cg_dir: 85 instead of 101 B per cell and one launch
+// fewer, but the down half reads its halo of r and q, twice that of b.  Where the
+// five vectors stay in the last-level cache (n <= 160) that pays: 128^3 steps
+// 3090 -> 3022 us, 64^3 1434 -> 1366; from HBM it does not: 192^3 5163 -> 5216.
+bool cg_fuses(const hipib_ctx* ctx) {
+    return marched(ctx, ctx->n) && ctx->n > kSmallMax && !(exact_coarse(ctx) && ctx->exact_level == 0) &&
+           5.0 * sizeof(double) * (double)ctx->n3 <= 160e6;
+}
+
+// One preconditioned conjugate-gradient iteration of the Poisson solve, number
+// it of the solve.  An iteration's step of r and its stop test are left to the
+// finest-level down half of the next iteration (which then reads r and q
+// instead of r) and its step of x to the next k_cg_dir, when the next one is
+// enqueued with it; `last` ends the batch with k_cg_update, `follows` says that
+// the iteration before was left open.
+hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc, int it, bool follows, bool last) {
     const int n = ctx->n;
     const int64_t n3 = ctx->n3;
     const double h = 1.0 / n, c = oc.nu / (h * h);
-    const int nb = sum_blocks(n3);
-    double *r = ctx->kv[0], *z = ctx->kv[1], *p = ctx->kv[2], *q = ctx->kv[3];
+    const int nb = sum_blocks(n3), slot = it & 1;
+    double *z = ctx->kv[1], *p = ctx->kv[2], *q = ctx->kv[3];
     const bool mixed = ctx->cfg.precision == HIPIB_MIXED;
-    const int64_t np = norm_parts(n);
     const double zb = mixed ? 4.0 : 8.0;   // bytes of a z value
-    // z = M r; the preconditioner's last two half-sweeps sum r.z and z.q when
-    // it post-smooths the finest level, else k_cg_dots does
+    const int npq = (int)norm_parts(n);
+    double* const pq = ctx->part + cg_pq_offset(n);
+    double* r = ctx->cg_r;
+    if (follows) {
+        // (b is not needed once r is: its second component holds every other r)
+        double* const other = r == ctx->kv[0] ? ctx->bpk + n3 : ctx->kv[0];
+        ctx->cg_update = hipib_ctx::CgUpdate{true, r, other, q, pq, npq, 1 - slot};
+        ctx->cg_r = r = other;
+    }
+    // z = M r; the preconditioner's up half (or its last two half-sweeps) sums r.z
+    // and z.q when it post-smooths the finest level, else k_cg_dots does
     ctx->cg_dots = hipib_ctx::CgDotsReq{r, q, 0};
     hipib_status vs;
     if (mixed) vs = vcycle<float>(ctx, 0, LevelPtr<float>{ctx->e32, ctx->r32, n3}, 1, oc, true);
     else vs = vcycle<double>(ctx, 0, LevelPtr<double>{z, r, n3}, 1, oc, true);
     const int64_t fused = ctx->cg_dots.parts;
     ctx->cg_dots = hipib_ctx::CgDotsReq{};
+    ctx->cg_update = hipib_ctx::CgUpdate{};
     HIPIB_TRY(vs);
     int64_t dparts = fused;
     if (fused == 0) {
@@ -2206,28 +2312,33 @@ hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc) {
                                r, z, q, n3, ctx->st, ctx->part, nb));
         dparts = nb;
     }
-    HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_REDUCE, 16.0 * dparts, k_cg_scalars, dim3(1), dim3(1024), 0, ctx->part,
-                       dparts, dparts, ctx->st));
-    if (mixed)
-        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_DIR, (32.0 + zb) * n3, k_cg_dir<float>, norm_grid(n, 1), dim3(TX, TY),
-                           0, ctx->e32, p, q, n, oc.sigma, c, ctx->st, ctx->part));
-    else
-        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_DIR, (32.0 + zb) * n3, k_cg_dir<double>, norm_grid(n, 1), dim3(TX, TY),
-                           0, z, p, q, n, oc.sigma, c, ctx->st, ctx->part));
-    // (alpha is reduced by k_cg_update itself: its ||r||^2 partials go after p.q's)
+    const bool fuses = cg_fuses(ctx);
+    const int first = it == 0 ? 1 : 0;
+    if (!fuses)
+        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_REDUCE, 16.0 * dparts, k_cg_scalars, dim3(1), dim3(1024), 0, ctx->part,
+                           dparts, dparts, ctx->st, first, slot));
+    double* const xs = follows ? ctx->sx : nullptr;
+    auto dir = [&](auto* zt) {
+        using TZ = std::remove_pointer_t<decltype(zt)>;
+        return launch_k(ctx, HIPIB_TIMER_CG_DIR, (32.0 + zb + (xs ? 16.0 : 0.0)) * (double)n3,
+                        fuses ? k_cg_dir<TZ, true> : k_cg_dir<TZ, false>, norm_grid(n, 1), dim3(TX, TY), 0, zt, p, q, xs, n,
+                        oc.sigma, c, ctx->st, ctx->part, dparts, dparts, first, slot, pq);
+    };
+    HIPIB_TRY(mixed ? dir(ctx->e32) : dir(z));
+    if (!last) return HIPIB_OK;
     const int nbu = update_blocks(n3);
     HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_UPDATE, (mixed ? 52.0 : 48.0) * n3, k_cg_update, dim3(nbu), dim3(kUpdThreads), 0,
-                       ctx->sx, r, p, q, n3, ctx->st, mixed ? ctx->r32 : nullptr, ctx->part, np, ctx->part + np));
-    return finalize_at(ctx, np, nbu, nbu, 1, FIN_CYCLE_R, 0.0);
+                       ctx->sx, r, p, q, n3, ctx->st, slot, mixed ? ctx->r32 : nullptr, pq, npq,
+                       ctx->part + cg_norm_offset(n)));
+    return finalize_at(ctx, cg_norm_offset(n), nbu, nbu, 1, FIN_CYCLE_R, 0.0);
 }
 
 bool use_cg(const hipib_ctx* ctx, const OpCoef& oc, int ncomp) {
     return oc.poisson && ncomp == 1 && ctx->cfg.mg_krylov && ctx->kv[0] != nullptr;
 }
 
-// one top-level cycle on the packed FP64 solution
+// one top-level plain cycle on the packed FP64 solution
 hipib_status cycle(hipib_ctx* ctx, int ncomp, const OpCoef& oc) {
-    if (use_cg(ctx, oc, ncomp)) return cg_iteration(ctx, oc);
     const int nb = sum_blocks(ctx->n3);
     if (ctx->cfg.precision == HIPIB_MIXED) {
         HIPIB_TRY(vcycle<float>(ctx, 0, LevelPtr<float>{ctx->e32, ctx->r32, ctx->n3}, ncomp, oc, true));
@@ -2402,12 +2513,17 @@ hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b
     k_zero_requested<<<dim3(nb, ncomp), 256, 0, ctx->stream>>>(xpk, ctx->n3, ctx->n3, ctx->st);
     HIPIB_HIP(hipGetLastError());
 
+    const bool cg = use_cg(ctx, oc, ncomp), fuses = cg && cg_fuses(ctx);
+    ctx->cg_r = ctx->kv[0];
     int enqueue = ctx->predicted[op] > 0 ? ctx->predicted[op] : 1;
     int total = 0;
     const int limit =
         (ctx->cfg.mg_fixed_cycles > 0 ? ctx->cfg.mg_fixed_cycles : ctx->cfg.mg_max_cycles) + 1;
     while (true) {
-        for (int e = 0; e < enqueue; ++e) HIPIB_TRY(cycle(ctx, ncomp, oc));
+        for (int e = 0; e < enqueue; ++e) {
+            if (!cg) HIPIB_TRY(cycle(ctx, ncomp, oc));
+            else HIPIB_TRY(cg_iteration(ctx, oc, total + e, fuses && e > 0, !fuses || e + 1 == enqueue));
+        }
         total += enqueue;
         HIPIB_TRY(sync_state(ctx));
         const MGState& s = *ctx->st_host;
@@ -2419,11 +2535,11 @@ hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b
         enqueue = 1;
     }
     *mean_ok = oc.poisson && ctx->st_host->status == HIPIB_OK;
-    if (*mean_ok && use_cg(ctx, oc, ncomp) && ctx->st_host->cycles[0] > 0) {
-        // the last conjugate-gradient update left the partial sums of x after
-        // its ||r||^2 partials (later enqueued cycles were no-ops)
+    if (*mean_ok && cg && ctx->st_host->cycles[0] > 0) {
+        // the k_cg_update of the last batch that did not start converged left the
+        // partial sums of x after its ||r||^2 partials
         const int nbu = update_blocks(ctx->n3);
-        HIPIB_TRY(finalize_at(ctx, norm_parts(ctx->n) + nbu, nbu, nbu, 1, FIN_MEAN_ALL, 1.0 / (double)ctx->n3));
+        HIPIB_TRY(finalize_at(ctx, cg_norm_offset(ctx->n) + nbu, nbu, nbu, 1, FIN_MEAN_ALL, 1.0 / (double)ctx->n3));
     } else if (*mean_ok) {
         k_sum_partials<<<dim3(nb, ncomp), 256, 0, ctx->stream>>>(xpk, ctx->n3, ctx->n3, 0, nullptr, ctx->part,
                                                                  nb);

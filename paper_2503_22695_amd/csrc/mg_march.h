@@ -58,12 +58,27 @@ struct MarchArgs {
     int64_t cs, ccs;  // component strides of the level and of the next one
     T c, inv_diag, sigma, omega;
     const MGState* st;
-    // MARCH_DOTS: r (mixed mode: the FP64 residual; FP64: b itself) and q; partial
+    // MARCH_DOTS: r (mixed mode: the FP64 residual; FP64: b itself) and q (also of CG); partial
     // sums of MARCH_DOTS and MARCH_NORM (pstride apart: r.z and z.q, or the components)
     const double* rd;
     const double* qd;
     double* part;
     int64_t pstride;
+};
+
+// (arguments of their own: 64 B more cost each launch of the other passes 0.5 us)
+template <typename T>
+struct MarchCgArgs : MarchArgs<T> {
+    // CG: b is formed here as r = rold - alpha qd (mixed mode: r / ||b||, kept in b32),
+    // alpha = *rz / (the sum of the npq partials pq), kept in the state; r of the box
+    // goes to rnew and the partial sums of ||r||^2 to part
+    const double* rold;
+    double* rnew;
+    float* b32;
+    const double* pq;
+    int npq;
+    const double* rz;
+    double* alpha;
 };
 
 constexpr int kMarchAhead = 4;        // planes read ahead
@@ -120,6 +135,26 @@ __device__ __forceinline__ void put_byte(T* base, int64_t o, uint32_t lane, T v)
     *(global_t<T>*)(g + lane) = v;
 }
 
+// alpha = rz / (sum of the npq partials of p.q), for every thread of a workgroup of
+// whole wavefronts; red: 8 doubles of LDS, free again on return.  The order of the
+// sum is that of 512 threads whatever the workgroup, so that a step taken by
+// k_cg_update and one taken by a down half are the same to the bit.
+__device__ __forceinline__ double cg_alpha(const double* __restrict__ pq, int npq, double rz, double* red) {
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    for (int w = threadIdx.x >> 6; w < 8; w += nw) {
+        double a = 0.0;
+        for (int t = 64 * w + lane; t < npq; t += 512) a += pq[t];
+        for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
+        if (lane == 0) red[w] = a;
+    }
+    __syncthreads();
+    double a = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) a += red[w];
+    __syncthreads();
+    return a != 0.0 ? rz / a : 0.0;
+}
+
 // a copy in registers of its own: without it a value read ahead stays where the
 // load put it, the next load into its slot goes elsewhere, and the loop ends
 // by moving loads in flight (and so by waiting for them)
@@ -134,9 +169,9 @@ __device__ __forceinline__ float own_copy(float v) {
     return r;
 }
 
-template <typename T, int SRC, int NS, bool SOR, int RES>
+template <typename T, int SRC, int NS, bool SOR, int RES, bool CG = false>
 __global__ void __launch_bounds__(kMarchThreads)
-k_march(MarchArgs<T> A) {
+k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
     constexpr int PF = kMarchAhead;
     constexpr int DH = march_halo(NS, RES);
     constexpr int q0 = SRC == MARCH_GUESS ? 1 : 0;           // colour of the source
@@ -219,9 +254,19 @@ k_march(MarchArgs<T> A) {
     };
     Plane nS = plane_at(zs), nR = plane_at(zs - FR), nB = plane_at(zs - FB);
     int zread = zs;                                          // (past the last step: its planes again)
+    double pr[PF][2], pq[PF][2], alpha = 0.0;                // CG: r and q in place of b
+    constexpr int D8 = 8 / (int)sizeof(T);
+    const double inv_bn = CG && sizeof(T) == 4 ? 1.0 / A.st->bn[0] : 1.0;
     auto read_plane = [&](int u) {
-        pb[u][0] = at_byte(bR, nR.o, goff);
-        pb[u][1] = at_byte(bB, nB.o, goff);
+        if constexpr (CG) {
+            pr[u][0] = at_byte(A.rold, D8 * nR.o, D8 * goff);
+            pq[u][0] = at_byte(A.qd, D8 * nR.o, D8 * goff);
+            pr[u][1] = at_byte(A.rold + half3, D8 * nB.o, D8 * goff);
+            pq[u][1] = at_byte(A.qd + half3, D8 * nB.o, D8 * goff);
+        } else {
+            pb[u][0] = at_byte(bR, nR.o, goff);
+            pb[u][1] = at_byte(bB, nB.o, goff);
+        }
         if (SRC != MARCH_ZERO) px[u] = at_byte(xs, nS.o, goff);
         if (SRC == MARCH_GUESS && SOR) po[u] = at_byte(xr, nS.o, goff);
         if (zread < zlast) {
@@ -233,6 +278,10 @@ k_march(MarchArgs<T> A) {
     };
 #pragma unroll
     for (int u = 0; u < PF; ++u) read_plane(u);
+    if constexpr (CG) {
+        alpha = cg_alpha(A.pq, A.npq, *A.rz, reinterpret_cast<double*>(march_lds));
+        if (blk == 0 && tid == 0) *A.alpha = alpha;
+    }
 
     // coarse correction: yI(K) = e interpolated along y at coarse plane K; the
     // row value of fine plane z is its interpolation along z
@@ -343,7 +392,7 @@ k_march(MarchArgs<T> A) {
         }
     };
 
-    // ||b - A x||^2 over the box: the residual of the colour relaxed last is
+    // ||b - A x||^2 (CG: ||r||^2) over the box: the residual of the colour relaxed last is
     // diag (1 - omega) / omega times its last change (none without over-relaxation)
     double rn = 0.0;
     const T wl = (T(1) / A.inv_diag) * (T(1) - A.omega) / A.omega;
@@ -373,8 +422,22 @@ k_march(MarchArgs<T> A) {
                 bh[0][a] = bh[0][a - 1];
                 bh[1][a] = bh[1][a - 1];
             }
-            bh[0][FR] = own_copy(pb[u][0]);
-            bh[1][FB] = own_copy(pb[u][1]);
+            if constexpr (CG) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const double r = pr[u][q] - alpha * pq[u][q];
+                    bh[q][q ? FB : FR] = sizeof(T) == 4 ? (T)(r * inv_bn) : (T)r;
+                    const int P = z - (q ? FB : FR);
+                    if (P >= k0 && P < k0 + zo && own) {
+                        rn += r * r;
+                        put_byte(A.rnew + q * half3, D8 * (P * pby), D8 * goff, r);
+                        if (sizeof(T) == 4) put_byte(A.b32 + q * half3, P * pby, goff, (float)(r * inv_bn));
+                    }
+                }
+            } else {
+                bh[0][FR] = own_copy(pb[u][0]);
+                bh[1][FB] = own_copy(pb[u][1]);
+            }
             const T pre1 = partial(1, zpar, hv[0][0], hv[0][1], oh);
             T v;
             if constexpr (SRC == MARCH_ZERO) {
@@ -450,8 +513,9 @@ k_march(MarchArgs<T> A) {
             lds_barrier();
         }
     }
-    if constexpr (RES == MARCH_DOTS || RES == MARCH_NORM) {
-        if (RES == MARCH_NORM) da = rn;
+    if constexpr (RES == MARCH_DOTS || RES == MARCH_NORM || CG) {
+        if (RES != MARCH_DOTS) da = rn;
+        if (CG) __syncthreads();             // (the restriction after the last barrier read LDS)
         double* const red = reinterpret_cast<double*>(march_lds);   // (the last barrier is behind every read)
         for (int o = 32; o > 0; o >>= 1) {
             da += __shfl_down(da, o, 64);

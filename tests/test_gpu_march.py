@@ -80,3 +80,28 @@ def test_exact_level(torch_dev, hp, ref, n, op, ncomp, mixed):
         lam = (0.0 if poisson else 1.0 / dt) + (1.0 if poisson else 0.01) * (e[:, None, None] + e[:, None] + e)
         lam[0, 0, 0] = np.inf if poisson else lam[0, 0, 0]
         assert_close(f"x[{d}]", host(xd)[d], np.real(np.fft.ifftn(np.fft.fftn(b[d]) / lam)), TOL)
+
+
+@pytest.mark.parametrize("n,mixed", [(48, 0), (64, 0), (96, 1), (128, 0)])
+def test_open_iterations_bitwise(torch_dev, hp, n, mixed):
+    """Conjugate gradients enqueued one iteration at a time (a context's first
+    solve, whose length it does not know) and all together (its second, where
+    an iteration leaves its steps of r and x to the next one's passes): the same
+    solution to the bit, also where fewer or more iterations are enqueued than
+    needed."""
+    torch = torch_dev
+    say("open iterations", n, mixed)
+    rng = np.random.default_rng(n)
+    b = rng.standard_normal((n, n, n))
+    b -= b.mean()
+    easy = np.cos(2 * np.pi * np.arange(n) / n) * np.ones((n, n, 1))   # an eigenvector: few iterations
+    ctx = plain_ctx(hp, n, precision=hp.MIXED if mixed else hp.FP64)
+    out = {}
+    for name, rhs in (("first", b), ("again", b), ("easy", easy), ("short", b), ("easy after", easy)):
+        x = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+        cyc, rr = ctx.mg_solve(hp.OP_POISSON, to_dev(torch, rhs), x)
+        assert rr[0] <= 1e-10
+        out[name] = (int(cyc[0]), host(x))
+    for one, other in (("first", "again"), ("first", "short"), ("easy", "easy after")):
+        assert out[one][0] == out[other][0]
+        assert np.array_equal(out[one][1], out[other][1]), (one, other)
