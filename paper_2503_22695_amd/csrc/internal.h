@@ -348,6 +348,18 @@ hipib_status launch_k(hipib_ctx* ctx, int kind, double bytes, void (*k)(KArgs...
 }
 
 // ---- small device helpers ----------------------------------------------------
+// Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
+// Renumbering so that XCD x runs the x-th contiguous eighth of the grid (in
+// x-fastest order: a slab of z-planes) keeps a stencil's neighbouring planes
+// in the same L2.  Identity when the grid is not a multiple of 8.
+__device__ __forceinline__ uint3 xcd_block() {
+    const unsigned gx = gridDim.x, gy = gridDim.y;
+    const unsigned nb = gx * gy * gridDim.z;
+    unsigned b = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+    if ((nb & 7u) == 0) b = (b & 7u) * (nb >> 3) + (b >> 3);
+    return make_uint3(b % gx, (b / gx) % gy, b / (gx * gy));
+}
+
 __device__ __forceinline__ int wrap_idx(int i, int n) {
     return i < 0 ? i + n : (i >= n ? i - n : i);
 }
