@@ -105,6 +105,13 @@ struct hipib_ctx {
         const double* pq = nullptr;
         int npq = 0, slot = 0;   // partials of p.q; slot of r.z
     } cg_update;
+    // stop test of a conjugate-gradient iteration (partials of ||r||^2 in part) that
+    // the next one's exact coarsest solve makes
+    struct StopLeft {
+        bool on = false;
+        int64_t offset = 0, parts = 0;
+        int mode = 0;
+    } stop_left;
     // set by a plain cycle on the iterate: its last fused pass also sums
     // ||b - A x||^2 (parts: the partials per component it wrote, 0 if none)
     bool want_norm = false;

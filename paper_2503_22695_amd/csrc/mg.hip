@@ -1043,6 +1043,44 @@ __global__ void k_zero_requested(double* __restrict__ x, int64_t cs, int64_t cou
         xc[t] = 0.0;
 }
 
+// the state of a component whose residual norm is rn: cycles, status and whether it goes on
+__device__ __forceinline__ void stop_decision(MGState* st, int comp, int mode, double rn, double rtol, int max_cycles,
+                                              int fixed_cycles) {
+    const double bn = st->bn[comp];
+    if (mode == FIN_INIT_R || mode == FIN_BNORM_INIT_R) {
+        st->cycles[comp] = 0;
+        st->zero_req[comp] = 0;
+    } else {
+        st->cycles[comp] += 1;
+    }
+    int act = 1;
+    if (!isfinite(bn)) {
+        st->status = HIPIB_E_NUMERIC;
+        act = 0;
+    } else if (bn == 0.0) {
+        st->zero_req[comp] = 1;
+        st->rn[comp] = 0.0;
+        act = 0;
+    } else {
+        st->rn[comp] = rn;
+        const double tol = (rtol > 1e3 * DBL_EPSILON ? rtol : 1e3 * DBL_EPSILON) * bn;
+        const int cyc = st->cycles[comp];
+        if (!isfinite(rn)) {
+            st->status = HIPIB_E_NUMERIC;
+            act = 0;
+        } else if (fixed_cycles > 0) {
+            act = cyc < fixed_cycles;
+        } else if (rn <= tol) {
+            act = 0;
+        } else if (cyc >= max_cycles) {
+            st->status = HIPIB_E_NOCONV;
+            act = 0;
+        }
+    }
+    st->active[comp] = act;
+    if (mode == FIN_CG_STEP && !act) st->x_pending = 1;
+}
+
 // Reduce the partials of each component (fixed order) and update the state.
 __global__ void __launch_bounds__(1024)
 k_finalize(const double* __restrict__ part, int64_t nparts, int64_t pstride, int ncomp, int mode,
@@ -1092,40 +1130,7 @@ k_finalize(const double* __restrict__ part, int64_t nparts, int64_t pstride, int
             } else if (mode == FIN_MEAN || mode == FIN_MEAN_ALL) {
                 st->mean[comp] = s * inv_count;
             } else {
-                const double bn = st->bn[comp];
-                if (mode == FIN_INIT_R || mode == FIN_BNORM_INIT_R) {
-                    st->cycles[comp] = 0;
-                    st->zero_req[comp] = 0;
-                } else {
-                    st->cycles[comp] += 1;
-                }
-                const double rn = sqrt(s);
-                int act = 1;
-                if (!isfinite(bn)) {
-                    st->status = HIPIB_E_NUMERIC;
-                    act = 0;
-                } else if (bn == 0.0) {
-                    st->zero_req[comp] = 1;
-                    st->rn[comp] = 0.0;
-                    act = 0;
-                } else {
-                    st->rn[comp] = rn;
-                    const double tol = (rtol > 1e3 * DBL_EPSILON ? rtol : 1e3 * DBL_EPSILON) * bn;
-                    const int cyc = st->cycles[comp];
-                    if (!isfinite(rn)) {
-                        st->status = HIPIB_E_NUMERIC;
-                        act = 0;
-                    } else if (fixed_cycles > 0) {
-                        act = cyc < fixed_cycles;
-                    } else if (rn <= tol) {
-                        act = 0;
-                    } else if (cyc >= max_cycles) {
-                        st->status = HIPIB_E_NOCONV;
-                        act = 0;
-                    }
-                }
-                st->active[comp] = act;
-                if (mode == FIN_CG_STEP && !act) st->x_pending = 1;
+                stop_decision(st, comp, mode, sqrt(s), rtol, max_cycles, fixed_cycles);
             }
         }
         __syncthreads();
@@ -1318,12 +1323,36 @@ __device__ __forceinline__ void plane_operand(T (&f)[N / 4], const T* __restrict
     for (int t = 0; t < N / 4; ++t) f[t] = p[(4 * t + (lane >> 4)) * ld + m];
 }
 
-template <int N, typename T>
+// STOP: one workgroup more makes the stop test of the iteration before, which the
+// launch of k_finalize would (4.6 us of the 160 of an iteration at 128^3); the
+// others do not read `active` while it changes, and what they write is not used
+// where the test says stop.
+struct StopTest {
+    const double* part;   // sums of ||r||^2
+    int nparts, mode;
+    MGState* st;
+    double rtol;
+    int max_cycles, fixed_cycles;
+};
+
+template <int N, typename T, bool STOP>
 __global__ void __launch_bounds__(kPlaneThreads)
 k_exact_fwd_xy(const T* __restrict__ bg, int64_t cs, const T* __restrict__ tab, T* __restrict__ work,
-               const int32_t* __restrict__ active) {
+               const int32_t* __restrict__ active, std::conditional_t<STOP, StopTest, int> stop) {
     constexpr int NP = N + 1;
     __shared__ T U[N * NP];
+    if constexpr (STOP) {
+        if (blockIdx.x == N) {
+            __shared__ double red[16];
+            if (!stop.st->active[0]) return;   // uniform
+            double s = 0.0;
+            for (int t = threadIdx.x; t < stop.nparts; t += kPlaneThreads) s += stop.part[t];
+            s = block_sum(s, red);
+            if (threadIdx.x == 0)
+                stop_decision(stop.st, 0, stop.mode, sqrt(s), stop.rtol, stop.max_cycles, stop.fixed_cycles);
+            return;
+        }
+    }
     const int k = blockIdx.x, comp = blockIdx.y;
     const int lane = threadIdx.x & 63, ti = (threadIdx.x >> 7) * 16, tj = ((threadIdx.x >> 6) & 1) * 16;
     T a[N / 4], qx[N / 4], qy[N / 4];
@@ -1334,7 +1363,7 @@ k_exact_fwd_xy(const T* __restrict__ bg, int64_t cs, const T* __restrict__ tab, 
     }
     plane_operand<N>(qx, tab, N, tj, lane);
     plane_operand<N>(qy, tab, N, ti, lane);
-    if (!active[comp]) return;   // uniform
+    if (!STOP && !active[comp]) return;   // uniform
     Tile<T> u;                   // U[j][mx] = sum_i b[j][i] Q[i][mx]
 #pragma unroll
     for (int t = 0; t < N / 4; ++t) u.add(a[t], qx[t]);
@@ -1799,6 +1828,19 @@ double* state_field(const hipib_ctx* ctx, size_t offset) {
 int64_t cg_pq_offset(int n) { return 4 * norm_parts(n); }
 int64_t cg_norm_offset(int n) { return cg_pq_offset(n) + norm_parts(n); }
 
+// the stop test of a conjugate-gradient iteration that another one follows: left to
+// the exact coarsest solve where that has plane-parallel passes
+hipib_status leave_stop_test(hipib_ctx* ctx, int64_t parts, int mode) {
+    const int N = ctx->lv[ctx->exact_level].n;
+    if (!exact_coarse(ctx) || ctx->exact_level == 0 || (N != 32 && N != 24))
+        return finalize_at(ctx, cg_norm_offset(ctx->n), parts, parts, 1, mode, 0.0);
+    ctx->stop_left.on = true;
+    ctx->stop_left.offset = cg_norm_offset(ctx->n);
+    ctx->stop_left.parts = parts;
+    ctx->stop_left.mode = mode;
+    return HIPIB_OK;
+}
+
 template <typename T>
 hipib_status zero_t(hipib_ctx* ctx, T* p, int64_t count) {
     if (count <= 0) return HIPIB_OK;
@@ -1829,6 +1871,29 @@ const double* exact_table<double>(const hipib_ctx* ctx) { return ctx->coarse_tab
 template <>
 const float* exact_table<float>(const hipib_ctx* ctx) { return ctx->coarse_tab32; }
 
+// its three plane-parallel passes; the first also makes a stop test left to it
+template <int N, typename T>
+hipib_status plane_exact(hipib_ctx* ctx, LevelPtr<T> p, int ncomp, const OpCoef& oc) {
+    const dim3 pg(N, ncomp), pb(kPlaneThreads);
+    const int32_t* act = ctx->st->active;
+    const double bytes = 2.0 * sizeof(T) * N * N * N * ncomp;
+    const T* tab = exact_table<T>(ctx);
+    T* work = static_cast<T*>(ctx->coarse_work);
+    if (ctx->stop_left.on) {
+        const StopTest stop{ctx->part + ctx->stop_left.offset, (int)ctx->stop_left.parts, ctx->stop_left.mode, ctx->st,
+                            ctx->cfg.mg_rtol, ctx->cfg.mg_max_cycles, ctx->cfg.mg_fixed_cycles};
+        ctx->stop_left.on = false;
+        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, bytes, k_exact_fwd_xy<N, T, true>, dim3(N + 1), pb, 0, p.b,
+                           p.cs, tab, work, act, stop));
+    } else {
+        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, bytes, k_exact_fwd_xy<N, T, false>, pg, pb, 0, p.b, p.cs, tab,
+                           work, act, 0));
+    }
+    HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, bytes, k_exact_z<N, T>, pg, pb, 0, work, tab, (T)oc.sigma,
+                       (T)oc.nu, act));
+    return launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, bytes, k_exact_inv_xy<N, T>, pg, pb, 0, p.x, p.cs, tab, work, act);
+}
+
 // exact solve of the coarsest level l (the first with at most 32 cells per side)
 template <typename T>
 hipib_status coarse_exact(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoef& oc) {
@@ -1846,25 +1911,8 @@ hipib_status coarse_exact(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const
     if (n == 8)
         return launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, bytes, k_coarse_exact<8, T>, grid, blk,
                         exact_lds_words<8>() * sizeof(T), p.x, p.b, p.cs, tab, (T)oc.sigma, (T)oc.nu, act);
-    T* work = static_cast<T*>(ctx->coarse_work);
-    if (n == 32 || n == 24) {
-        const dim3 pg(n, ncomp), pb(kPlaneThreads);
-        const double wb = sizeof(T) * (double)ctx->lv[l].n3 * ncomp;
-        if (n == 32) {
-            HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_fwd_xy<32, T>, pg, pb, 0, p.b, p.cs,
-                               tab, work, act));
-            HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_z<32, T>, pg, pb, 0, work, tab,
-                               (T)oc.sigma, (T)oc.nu, act));
-            return launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_inv_xy<32, T>, pg, pb, 0, p.x, p.cs,
-                            tab, work, act);
-        }
-        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_fwd_xy<24, T>, pg, pb, 0, p.b, p.cs,
-                           tab, work, act));
-        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_z<24, T>, pg, pb, 0, work, tab,
-                           (T)oc.sigma, (T)oc.nu, act));
-        return launch_k(ctx, HIPIB_TIMER_SMALL_VCYCLE, wb * 2, k_exact_inv_xy<24, T>, pg, pb, 0, p.x, p.cs, tab,
-                        work, act);
-    }
+    if (n == 32) return plane_exact<32, T>(ctx, p, ncomp, oc);
+    if (n == 24) return plane_exact<24, T>(ctx, p, ncomp, oc);
     return fail(HIPIB_E_INVAL, "no exact coarse solve for n = %d", n);
 }
 
@@ -2162,7 +2210,7 @@ hipib_status vcycle(hipib_ctx* ctx, int l, LevelPtr<T> p, int ncomp, const OpCoe
             A.part = ctx->part + cg_norm_offset(n);
             HIPIB_TRY((march<MARCH_ZERO, 3, false, MARCH_RESTRICT, true>(
                 ctx, l, down, (24.0 + (sizeof(T) == 4 ? 4.0 : 0.0) + 5.0 / 8.0 * sizeof(T)) * (double)ctx->n3, A, 1, &boxes, C)));
-            HIPIB_TRY(finalize_at(ctx, cg_norm_offset(n), boxes, boxes, 1, FIN_CG_STEP, 0.0));
+            HIPIB_TRY(leave_stop_test(ctx, boxes, FIN_CG_STEP));
             if constexpr (sizeof(T) == 8) A.b = g.rnew;
         } else if (zero_guess)
             HIPIB_TRY((march<MARCH_ZERO, 3, false, MARCH_RESTRICT>(ctx, l, down, 13.0 / 8.0 * cell, A, ncomp)));
@@ -2263,8 +2311,8 @@ bool cg_fuses(const hipib_ctx* ctx) {
 // it of the solve.  An iteration's step of r and its stop test are left to the
 // finest-level down half of the next iteration (which then reads r and q
 // instead of r) and its step of x to the next k_cg_dir, when the next one is
-// enqueued with it; `last` ends the batch with k_cg_update, `follows` says that
-// the iteration before was left open.
+// enqueued with it and cg_fuses; `last` ends the batch with k_cg_update, `follows`
+// says that the iteration before was left open.
 hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc, int it, bool follows, bool last) {
     const int n = ctx->n;
     const int64_t n3 = ctx->n3;
@@ -2315,11 +2363,12 @@ hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc, int it, bool follows
                         oc.sigma, c, ctx->st, ctx->part, dparts, dparts, first, slot, pq);
     };
     HIPIB_TRY(mixed ? dir(ctx->e32) : dir(z));
-    if (!last) return HIPIB_OK;
+    if (!last && cg_fuses(ctx)) return HIPIB_OK;
     const int nbu = update_blocks(n3);
     HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_UPDATE, (mixed ? 52.0 : 48.0) * n3, k_cg_update, dim3(nbu), dim3(kUpdThreads), 0,
                        ctx->sx, r, p, q, n3, ctx->st, slot, mixed ? ctx->r32 : nullptr, pq, npq,
                        ctx->part + cg_norm_offset(n)));
+    if (!last) return leave_stop_test(ctx, nbu, FIN_CYCLE_R);
     return finalize_at(ctx, cg_norm_offset(n), nbu, nbu, 1, FIN_CYCLE_R, 0.0);
 }
 
@@ -2505,6 +2554,7 @@ hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b
 
     const bool cg = use_cg(ctx, oc, ncomp), fuses = cg && cg_fuses(ctx);
     ctx->cg_r = ctx->kv[0];
+    ctx->stop_left.on = false;
     int enqueue = ctx->predicted[op] > 0 ? ctx->predicted[op] : 1;
     int total = 0;
     const int limit =
@@ -2512,7 +2562,7 @@ hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b
     while (true) {
         for (int e = 0; e < enqueue; ++e) {
             if (!cg) HIPIB_TRY(cycle(ctx, ncomp, oc));
-            else HIPIB_TRY(cg_iteration(ctx, oc, total + e, fuses && e > 0, !fuses || e + 1 == enqueue));
+            else HIPIB_TRY(cg_iteration(ctx, oc, total + e, fuses && e > 0, e + 1 == enqueue));
         }
         total += enqueue;
         HIPIB_TRY(sync_state(ctx));

@@ -82,7 +82,7 @@ def test_exact_level(torch_dev, hp, ref, n, op, ncomp, mixed):
         assert_close(f"x[{d}]", host(xd)[d], np.real(np.fft.ifftn(np.fft.fftn(b[d]) / lam)), TOL)
 
 
-@pytest.mark.parametrize("n,mixed", [(48, 0), (64, 0), (96, 1), (128, 0)])
+@pytest.mark.parametrize("n,mixed", [(48, 0), (64, 0), (96, 1), (128, 0), (192, 0)])
 def test_open_iterations_bitwise(torch_dev, hp, n, mixed):
     """Conjugate gradients enqueued one iteration at a time (a context's first
     solve, whose length it does not know) and all together (its second, where
