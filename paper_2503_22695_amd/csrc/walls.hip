@@ -22,6 +22,24 @@ namespace hipib {
 namespace {
 
 constexpr int WT = 256;
+constexpr int WX = 64, WY = 4;   // a workgroup's tile of cells (one plane)
+
+// A thread's cell of ncomp components of an m^3 array, from a grid of (x tiles, y
+// tiles, component * m + plane): a flat index took three 64-bit divisions a cell.
+struct WallCell {
+    int d, i, j, k;
+    bool in;
+    int64_t at;
+    __device__ __forceinline__ explicit WallCell(int m) {
+        d = blockIdx.z / m;
+        k = blockIdx.z - d * m;
+        i = blockIdx.x * WX + threadIdx.x;
+        j = blockIdx.y * WY + threadIdx.y;
+        in = i < m && j < m;
+        at = i + (int64_t)m * (j + (int64_t)m * blockIdx.z);
+    }
+};
+dim3 wall_grid(int m, int ncomp) { return dim3((m + WX - 1) / WX, (m + WY - 1) / WY, m * ncomp); }
 
 // returns the sign (0: a wall face) and the box index of image index ip
 __device__ __forceinline__ int wall_src(int n, int ip, bool face, int* src) {
@@ -41,58 +59,53 @@ __device__ __forceinline__ int wall_src(int n, int ip, bool face, int* src) {
 // (one Dirichlet field, as the walled Helmholtz solve of hipib_mg_solve takes it)
 enum { W_EVEN = 0, W_VELOCITY = 1, W_ODD = 2 };
 
-// img[c][k'][j'][i'] = sign * box[c][k][j][i] (0 on wall faces), c < ncomp
-__global__ void __launch_bounds__(WT)
-k_wall_extend(const double* __restrict__ box, double* __restrict__ img, int n, int ncomp, int mode) {
+// img[c][k'][j'][i'] = sign * box[c][k][j][i] (0 on wall faces), c < ncomp.  IMG: box
+// is the box part of img itself, of which only the wall faces are written (no
+// cell that is written is read).  Bound by its writes; three components of a 128^3
+// image 17.6 us (25.8 with a flat index), and IMG one pass in place of a restriction
+// and an extension (31.4).
+template <bool IMG>
+__global__ void __launch_bounds__(WX * WY)
+k_wall_extend(const double* box, double* img, int n, int mode) {
     const int m = 2 * n;
-    const int64_t M3 = (int64_t)m * m * m, N3 = (int64_t)n * n * n;
-    const int64_t t = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (t >= ncomp * M3) return;
-    const int d = (int)(t / M3);
-    const int64_t r = t - d * M3;
-    const int ip = (int)(r % m), jp = (int)((r / m) % m), kp = (int)(r / ((int64_t)m * m));
+    const WallCell c(m);
+    if (!c.in) return;
     const bool vector = mode == W_VELOCITY;
     int i = 0, j = 0, k = 0;
-    const int si = wall_src(n, ip, vector && d == 0, &i);
-    const int sj = wall_src(n, jp, vector && d == 1, &j);
-    const int sk = wall_src(n, kp, vector && d == 2, &k);
+    const int si = wall_src(n, c.i, vector && c.d == 0, &i);
+    const int sj = wall_src(n, c.j, vector && c.d == 1, &j);
+    const int sk = wall_src(n, c.k, vector && c.d == 2, &k);
     double v = 0.0;
     if (si && sj && sk) {
+        if (IMG && c.i < n && c.j < n && c.k < n) return;   // a cell of the box: as it is
+        const int s = IMG ? m : n;
         const double sg = mode == W_EVEN ? 1.0 : (double)(si * sj * sk);
-        v = sg * box[d * N3 + i + (int64_t)n * (j + (int64_t)n * k)];
+        v = sg * box[i + (int64_t)s * (j + (int64_t)s * (k + (int64_t)s * c.d))];
     }
-    img[t] = v;
+    img[c.at] = v;
 }
 
 // box = the box part of img, the wall faces of velocity components zero
-__global__ void __launch_bounds__(WT)
-k_wall_restrict(const double* __restrict__ img, double* __restrict__ box, int n, int ncomp, int mode) {
-    const bool vector = mode == W_VELOCITY;
-    const int m = 2 * n;
-    const int64_t M3 = (int64_t)m * m * m, N3 = (int64_t)n * n * n;
-    const int64_t t = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (t >= ncomp * N3) return;
-    const int d = (int)(t / N3);
-    const int64_t r = t - d * N3;
-    const int i = (int)(r % n), j = (int)((r / n) % n), k = (int)(r / ((int64_t)n * n));
-    const bool wall = vector && ((d == 0 && i == 0) || (d == 1 && j == 0) || (d == 2 && k == 0));
-    box[t] = wall ? 0.0 : img[d * M3 + i + (int64_t)m * (j + (int64_t)m * k)];
+__global__ void __launch_bounds__(WX * WY)
+k_wall_restrict(const double* __restrict__ img, double* __restrict__ box, int n, int mode) {
+    const WallCell c(n);
+    if (!c.in) return;
+    const int64_t m = 2 * n;
+    const bool wall = mode == W_VELOCITY && (c.d == 0 ? c.i : c.d == 1 ? c.j : c.k) == 0;
+    box[c.at] = wall ? 0.0 : img[c.i + m * (c.j + m * (c.k + m * c.d))];
 }
 
 // box[d] += scale * sum over the image cells mapping to it of sign * img, d <
 // ncomp, summed in image-index order: the transpose of k_wall_extend for
 // velocity (mode W_VELOCITY) or an even cell-centred scalar (W_EVEN)
-__global__ void __launch_bounds__(WT)
-k_wall_fold(const double* __restrict__ img, double* __restrict__ box, int n, int ncomp, int mode,
-            double scale) {
+__global__ void __launch_bounds__(WX * WY)
+k_wall_fold(const double* __restrict__ img, double* __restrict__ box, int n, int mode, double scale) {
+    const WallCell cell(n);
+    if (!cell.in) return;
     const bool vector = mode == W_VELOCITY;
-    const int m = 2 * n;
-    const int64_t M3 = (int64_t)m * m * m, N3 = (int64_t)n * n * n;
-    const int64_t t = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (t >= ncomp * N3) return;
-    const int d = (int)(t / N3);
-    const int64_t r = t - d * N3;
-    const int ijk[3] = {(int)(r % n), (int)((r / n) % n), (int)(r / ((int64_t)n * n))};
+    const int m = 2 * n, d = cell.d;
+    const int64_t M3 = (int64_t)m * m * m;
+    const int ijk[3] = {cell.i, cell.j, cell.k};
     // per axis: the (up to two) image indices that map here, ascending, with signs
     int pre[3][2], sg[3][2], cnt[3];
     for (int a = 0; a < 3; ++a) {
@@ -114,27 +127,21 @@ k_wall_fold(const double* __restrict__ img, double* __restrict__ box, int n, int
             for (int a = 0; a < cnt[0]; ++a)
                 s += (double)(sg[0][a] * sg[1][b] * sg[2][c]) *
                      img[d * M3 + pre[0][a] + (int64_t)m * (pre[1][b] + (int64_t)m * pre[2][c])];
-    box[t] = box[t] + scale * s;
+    box[cell.at] = box[cell.at] + scale * s;
 }
 
 // the transpose of k_wall_restrict: img = box values in the box part (velocity
 // wall faces zero), zero in the images
-__global__ void __launch_bounds__(WT)
-k_wall_pad(const double* __restrict__ box, double* __restrict__ img, int n, int ncomp, int mode) {
-    const bool vector = mode == W_VELOCITY;
-    const int m = 2 * n;
-    const int64_t M3 = (int64_t)m * m * m, N3 = (int64_t)n * n * n;
-    const int64_t t = (int64_t)blockIdx.x * WT + threadIdx.x;
-    if (t >= ncomp * M3) return;
-    const int d = (int)(t / M3);
-    const int64_t r = t - d * M3;
-    const int ip = (int)(r % m), jp = (int)((r / m) % m), kp = (int)(r / ((int64_t)m * m));
+__global__ void __launch_bounds__(WX * WY)
+k_wall_pad(const double* __restrict__ box, double* __restrict__ img, int n, int mode) {
+    const WallCell c(2 * n);
+    if (!c.in) return;
     double v = 0.0;
-    if (ip < n && jp < n && kp < n) {
-        const bool wall = vector && ((d == 0 && ip == 0) || (d == 1 && jp == 0) || (d == 2 && kp == 0));
-        if (!wall) v = box[d * N3 + ip + (int64_t)n * (jp + (int64_t)n * kp)];
+    if (c.i < n && c.j < n && c.k < n) {
+        const bool wall = mode == W_VELOCITY && (c.d == 0 ? c.i : c.d == 1 ? c.j : c.k) == 0;
+        if (!wall) v = box[c.i + (int64_t)n * (c.j + (int64_t)n * (c.k + (int64_t)n * c.d))];
     }
-    img[t] = v;
+    img[c.at] = v;
 }
 
 // y = a x (element-wise), or y += a x
@@ -148,14 +155,20 @@ k_scale(const double* __restrict__ x, double* __restrict__ y, double a, int64_t 
 unsigned blocks_for(int64_t count) { return (unsigned)((count + WT - 1) / WT); }
 
 hipib_status extend(hipib_ctx* ctx, const double* box, double* img, int ncomp, int mode) {
-    const int64_t M3 = ctx->img->n3;
-    k_wall_extend<<<blocks_for(ncomp * M3), WT, 0, ctx->stream>>>(box, img, ctx->n, ncomp, mode);
+    k_wall_extend<false><<<wall_grid(2 * ctx->n, ncomp), dim3(WX, WY), 0, ctx->stream>>>(box, img, ctx->n, mode);
+    HIPIB_HIP(hipGetLastError());
+    return HIPIB_OK;
+}
+
+// img = the extension of its own box part
+hipib_status mirror(hipib_ctx* ctx, double* img, int ncomp, int mode) {
+    k_wall_extend<true><<<wall_grid(2 * ctx->n, ncomp), dim3(WX, WY), 0, ctx->stream>>>(img, img, ctx->n, mode);
     HIPIB_HIP(hipGetLastError());
     return HIPIB_OK;
 }
 
 hipib_status restrict_box(hipib_ctx* ctx, const double* img, double* box, int ncomp, int mode) {
-    k_wall_restrict<<<blocks_for(ncomp * ctx->n3), WT, 0, ctx->stream>>>(img, box, ctx->n, ncomp, mode);
+    k_wall_restrict<<<wall_grid(ctx->n, ncomp), dim3(WX, WY), 0, ctx->stream>>>(img, box, ctx->n, mode);
     HIPIB_HIP(hipGetLastError());
     return HIPIB_OK;
 }
@@ -164,13 +177,13 @@ hipib_status restrict_box(hipib_ctx* ctx, const double* img, double* box, int nc
 hipib_status fold(hipib_ctx* ctx, const double* img, double* box, int ncomp, int mode, double s,
                   bool acc) {
     if (!acc) HIPIB_TRY(launch_zero(ctx, box, ncomp * ctx->n3));
-    k_wall_fold<<<blocks_for(ncomp * ctx->n3), WT, 0, ctx->stream>>>(img, box, ctx->n, ncomp, mode, s);
+    k_wall_fold<<<wall_grid(ctx->n, ncomp), dim3(WX, WY), 0, ctx->stream>>>(img, box, ctx->n, mode, s);
     HIPIB_HIP(hipGetLastError());
     return HIPIB_OK;
 }
 
 hipib_status pad(hipib_ctx* ctx, const double* box, double* img, int ncomp, int mode) {
-    k_wall_pad<<<blocks_for(ncomp * ctx->img->n3), WT, 0, ctx->stream>>>(box, img, ctx->n, ncomp, mode);
+    k_wall_pad<<<wall_grid(2 * ctx->n, ncomp), dim3(WX, WY), 0, ctx->stream>>>(box, img, ctx->n, mode);
     HIPIB_HIP(hipGetLastError());
     return HIPIB_OK;
 }
@@ -259,15 +272,12 @@ hipib_status walled_ns_step(hipib_ctx* ctx, const double* f, double* u, double* 
     HIPIB_TRY(extend(ctx, p, ctx->w_p, 1, W_EVEN));
     // g = (rho/dt) u - rho C_h(u) + f, C_h = C_{h/2} / 2; restricted (wall faces 0) and mirrored
     HIPIB_TRY(launch_rhs_build_coef(img, ctx->w_u, ctx->w_f, ctx->w_g, rho / dt, 0.5 * rho));
-    HIPIB_TRY(restrict_box(ctx, ctx->w_g, ctx->w_box, 3, W_VELOCITY));
-    HIPIB_TRY(extend(ctx, ctx->w_box, ctx->w_g, 3, W_VELOCITY));
+    HIPIB_TRY(mirror(ctx, ctx->w_g, 3, W_VELOCITY));
     HIPIB_TRY(mg_solve(img, HIPIB_OP_HELMHOLTZ, 3, ctx->w_g, ctx->w_u, cyc, rr));
-    HIPIB_TRY(restrict_box(ctx, ctx->w_u, ctx->w_box, 3, W_VELOCITY));
-    HIPIB_TRY(extend(ctx, ctx->w_box, ctx->w_u, 3, W_VELOCITY));
+    HIPIB_TRY(mirror(ctx, ctx->w_u, 3, W_VELOCITY));
     // b = 4 (-(rho/dt) D_h u*) = -2 (rho/dt) D_{h/2} u*: box part mirrored evenly
     HIPIB_TRY(launch_divergence_rhs_coef(img, ctx->w_u, ctx->w_b, 2.0 * (rho / dt)));
-    HIPIB_TRY(restrict_box(ctx, ctx->w_b, ctx->w_box, 1, W_EVEN));
-    HIPIB_TRY(extend(ctx, ctx->w_box, ctx->w_b, 1, W_EVEN));
+    HIPIB_TRY(mirror(ctx, ctx->w_b, 1, W_EVEN));
     HIPIB_TRY(mg_remove_mean(img, ctx->w_b, 0));
     HIPIB_TRY(mg_solve(img, HIPIB_OP_POISSON, 1, ctx->w_b, ctx->w_p, cyc + 3, rr + 3));
     // u = u* - (dt/rho) G_h p, G_h = G_{h/2} / 2
