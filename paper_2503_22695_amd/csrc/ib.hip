@@ -18,12 +18,19 @@
 // walks the nodes in the same tile order so a wavefront gathers from a small
 // neighbourhood.  Summation order is not fixed, so results agree with a serial
 // sum to rounding.
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "delta.h"
 
 namespace hipib {
 namespace {
+
+// work items (the list's length is not known to the host) share at most so many
+// workgroups: as many as run at once (8 to a CU); a grid of the list's capacity is
+// mostly workgroups without an item.
+constexpr int64_t kTileBlocks = 2048;
 
 // ---------------------------------------------------------------------------
 // Workspace of hipib_spread_noalloc: the node bins live in one static device
@@ -52,7 +59,8 @@ __global__ void __launch_bounds__(256) k_zero_i32(int32_t* __restrict__ p, int64
 // tile of each node and its rank inside the tile.  Consecutive nodes of a
 // mesh mostly share a tile, so the lanes of a wavefront with equal tiles are
 // grouped and one lane adds the group's size to the count (one atomic per
-// distinct tile per wavefront instead of one per node).
+// distinct tile per wavefront instead of one per node, all of them at once: 7.8 us
+// for 126000 nodes; waiting for each before the next group, 9.2).
 __global__ void k_clear_flag(int32_t* flag) {
     if (threadIdx.x == 0) *flag = 0;
 }
@@ -81,18 +89,21 @@ k_bin_count(const double* __restrict__ X, int nn, int n, int T, int ta, double i
     }
     const int lane = (int)__lane_id();
     unsigned long long pending = __ballot(valid);
-    int rank = 0;
+    int first = lane, rank = 0, size = 0;
     while (pending) {  // uniform over the wavefront
         const int leader = __ffsll((long long)pending) - 1;
-        const int key = __shfl(tile, leader, 64);
-        const bool mine = valid && tile == key;
+        const bool mine = valid && tile == __shfl(tile, leader, 64);
         const unsigned long long m = __ballot(mine);
-        int base = 0;
-        if (lane == leader) base = atomicAdd(count + key, __popcll(m));
-        base = __shfl(base, leader, 64);
-        if (mine) rank = base + __popcll(m & ((1ull << lane) - 1ull));
+        if (mine) {
+            first = leader;
+            rank = __popcll(m & ((1ull << lane) - 1ull));
+            size = __popcll(m);
+        }
         pending &= ~m;
     }
+    int base = 0;
+    if (valid && lane == first) base = atomicAdd(count + tile, size);
+    rank += __shfl(base, first, 64);
     if (valid) node_rank[q] = rank;
 }
 
@@ -101,46 +112,73 @@ k_bin_count(const double* __restrict__ X, int nn, int n, int T, int ta, double i
 // (tile, first rank) pairs, so a tile crowded with nodes is spread by several
 // workgroups.  Counts are reset to 0 for the next binning.  When given,
 // lfirst[t] receives the list index of tile t's first work item.
+// One workgroup in rounds of 4096 tiles, four to a thread, the next round's counts
+// read ahead.  (Each thread a contiguous share of all tiles, one count at a time:
+// a chain of reads, 8.2 us for 16^3 tiles and 57 for 24^3 in place of 5.8 and 31.)
 __global__ void __launch_bounds__(1024)
 k_bin_scan(int32_t* __restrict__ count, int64_t ntiles, int32_t* __restrict__ off,
            int32_t* __restrict__ list, int32_t* __restrict__ nlist, int32_t* __restrict__ lfirst) {
-    __shared__ int32_t s_sum[1024], s_nz[1024];
-    const int tid = threadIdx.x;
-    const int64_t per = (ntiles + 1023) / 1024;
-    const int64_t beg = tid * per < ntiles ? tid * per : ntiles;
-    const int64_t end = beg + per < ntiles ? beg + per : ntiles;
-    int32_t sum = 0, nz = 0;
-    for (int64_t i = beg; i < end; ++i) {
-        sum += count[i];
-        nz += (count[i] + kSpreadChunk - 1) / kSpreadChunk;
-    }
-    s_sum[tid] = sum;
-    s_nz[tid] = nz;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int32_t a = tid >= o ? s_sum[tid - o] : 0;
-        const int32_t b = tid >= o ? s_nz[tid - o] : 0;
-        __syncthreads();
-        s_sum[tid] += a;
-        s_nz[tid] += b;
-        __syncthreads();
-    }
-    int32_t run = s_sum[tid] - sum, lrun = s_nz[tid] - nz;
-    for (int64_t i = beg; i < end; ++i) {
-        off[i] = run;
-        if (lfirst) lfirst[i] = lrun;
-        const int32_t c = count[i];
-        run += c;
-        for (int32_t r = 0; r < c; r += kSpreadChunk) {
-            list[2 * lrun] = (int32_t)i;
-            list[2 * lrun + 1] = r;
-            ++lrun;
+    __shared__ int32_t wsum[2][2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto read = [&](int64_t i, int32_t* c) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c[r] = i + r < ntiles ? count[i + r] : 0;
+    };
+    int32_t c[4], run0 = 0, list0 = 0;   // (totals of the rounds before)
+    read(4 * tid, c);
+    for (int64_t base = 0, round = 0; base < ntiles; base += 4096, ++round) {
+        const int64_t i0 = base + 4 * tid;
+        int32_t next[4] = {0, 0, 0, 0}, chunks[4];
+        if (base + 4096 < ntiles) read(i0 + 4096, next);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) chunks[r] = (c[r] + kSpreadChunk - 1) / kSpreadChunk;
+        const int32_t sum = c[0] + c[1] + c[2] + c[3], nz = chunks[0] + chunks[1] + chunks[2] + chunks[3];
+        int32_t a = sum, b = nz;         // inclusive over the wavefront
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t pa = __shfl_up(a, o, 64), pb = __shfl_up(b, o, 64);
+            if (lane >= o) {
+                a += pa;
+                b += pb;
+            }
         }
-        count[i] = 0;
+        int32_t (*const ws)[16] = wsum[round & 1];
+        if (lane == 63) {
+            ws[0][wave] = a;
+            ws[1][wave] = b;
+        }
+        __syncthreads();
+        int32_t run = run0 + a - sum, lrun = list0 + b - nz;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int32_t ta = ws[0][w], tb = ws[1][w];
+            if (w < wave) {
+                run += ta;
+                lrun += tb;
+            }
+            run0 += ta;
+            list0 += tb;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t i = i0 + r;
+            if (i < ntiles) {
+                off[i] = run;
+                if (lfirst) lfirst[i] = lrun;
+                count[i] = 0;
+                for (int32_t q = 0; q < c[r]; q += kSpreadChunk) {
+                    list[2 * lrun] = (int32_t)i;
+                    list[2 * lrun + 1] = q;
+                    ++lrun;
+                }
+                run += c[r];
+            }
+            c[r] = next[r];
+        }
     }
-    if (tid == 1023) {
-        off[ntiles] = s_sum[1023];
-        *nlist = s_nz[1023];
+    if (tid == 0) {
+        off[ntiles] = run0;
+        *nlist = list0;
     }
 }
 
@@ -159,7 +197,8 @@ k_bin_scatter(const int32_t* __restrict__ node_tile, const int32_t* __restrict__
 // workgroups of a single box of all three lattices).  Ranks inside the chunk
 // are dealt to threads with an odd stride, so the lanes of a wavefront take
 // nodes that are far apart in mesh order, which keeps apart the LDS addresses
-// they add to in the same instruction.  TW: type of the
+// they add to in the same instruction.  (Four threads to a node, a plane each: more
+// of an instruction's additions collide, 35 -> 48 us at 128^3.)  TW: type of the
 // weights and their products (the lattice coordinate, its floor and the
 // fractional offset are always FP64); the LDS box and the grid accumulate in
 // FP64, since neighbouring nodes' forces partly cancel there.
@@ -219,8 +258,8 @@ k_spread_tiles(const double* __restrict__ X, const double* __restrict__ F, doubl
             if (v != 0.0) {
                 const int r = e;
                 const int lx = r % E, ly = (r / E) % E, lz = r / (E * E);
-                const int gx = wrap_mod(tb[0] - 2 + lx, n), gy = wrap_mod(tb[1] - 2 + ly, n),
-                          gz = wrap_mod(tb[2] - 2 + lz, n);
+                const int gx = wrap_idx(tb[0] - 2 + lx, n), gy = wrap_idx(tb[1] - 2 + ly, n),
+                          gz = wrap_idx(tb[2] - 2 + lz, n);   // (within two cells of the grid)
                 const int64_t g = f_packed ? pk(gx, gy, gz, n) : gx + (int64_t)n * (gy + (int64_t)n * gz);
                 atomicAdd(f + d * n3 + g, v);
             }
@@ -235,9 +274,13 @@ k_spread_tiles(const double* __restrict__ X, const double* __restrict__ F, doubl
 // each velocity component around the tile (E = T + 4, from T * tile - 2, the
 // reach of every node's 4x4x4 stencils on all three staggered lattices) is
 // staged in LDS with coalesced row loads, so the stencil values a tile's nodes
-// share are fetched from L2 once; each node's 3 x 64-term sums then read LDS,
-// in the same weights and order as a direct gather.  TW: type of the box, the
-// weights and the accumulation.
+// share are fetched from L2 once, all of a thread's reads in flight (three components
+// of a cell to a thread); each node's 3 x 64-term sums then read LDS.  At most 64
+// nodes: four threads to a node, one plane of its stencils each, so that the sums of
+// a sparse item are a quarter as long (216 elements at 32^3: 14.6 -> 6.7 us, 126000
+// nodes at 128^3 30.6 -> 26.0, 281000 at 192^3 53.6 -> 40.7; four threads for every item
+// 31.4 at 128^3).  In FP32 one thread sums in the order of a direct gather, which
+// FP32 results depend on.  TW: type of the box, the weights and the accumulation.
 template <int T, typename TW>
 __global__ void __launch_bounds__(kSpreadChunk)
 k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict__ U, double* Xupd, double dt,
@@ -250,60 +293,84 @@ k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict
     for (int li = blockIdx.x; li < ntl; li += gridDim.x) {
         const int tile = list[2 * li];
         const int tb[3] = {T * (tile % ta), T * ((tile / ta) % ta), T * (tile / (ta * ta))};
+        const int first = off[tile] + list[2 * li + 1], cnt = min(off[tile + 1] - first, kSpreadChunk);
+        // the box's cells, the three components of a cell by the same thread
+        constexpr int R = (E3 + kSpreadChunk - 1) / kSpreadChunk;
+        TW v[R][3];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = min((int)threadIdx.x + r * kSpreadChunk, E3 - 1);
+            const int lx = e % E, ly = (e / E) % E, lz = e / (E * E);
+            const int gx = wrap_idx(tb[0] - 2 + lx, n), gy = wrap_idx(tb[1] - 2 + ly, n),
+                      gz = wrap_idx(tb[2] - 2 + lz, n);   // (within two cells of the grid)
+            const int64_t g = gx + (int64_t)n * (gy + (int64_t)n * gz);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) v[r][d] = (TW)u[d * n3 + g];
+        }
         __syncthreads();   // the previous item's reads of the box are done
-        for (int e = threadIdx.x; e < 3 * E3; e += blockDim.x) {
-            const int d = e / E3, r = e - d * E3;
-            const int lx = r % E, ly = (r / E) % E, lz = r / (E * E);
-            const int gx = wrap_mod(tb[0] - 2 + lx, n), gy = wrap_mod(tb[1] - 2 + ly, n),
-                      gz = wrap_mod(tb[2] - 2 + lz, n);
-            box[e] = (TW)u[d * n3 + gx + (int64_t)n * (gy + (int64_t)n * gz)];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int e = threadIdx.x + r * kSpreadChunk;
+            if (e < E3)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) box[d * E3 + e] = v[r][d];
         }
         __syncthreads();
-        const int idx = off[tile] + list[2 * li + 1] + threadIdx.x;
-        if (idx < off[tile + 1]) {
-            const int q = perm[idx];
-            const double X0 = X[3 * q], X1 = X[3 * q + 1], X2 = X[3 * q + 2];
-            const double xs[3] = {safe_coord(X0 * inv_h), safe_coord(X1 * inv_h), safe_coord(X2 * inv_h)};
-            int cw[3];
-            for (int e = 0; e < 3; ++e) cw[e] = wrap_mod((int)floor(xs[e]), n);
-            TW Uq[3];
-            for (int d = 0; d < 3; ++d) {
-                int ls[3];
-                TW w[3][4];
-                for (int e = 0; e < 3; ++e) {
-                    const double r = xs[e] - (e == d ? 0.0 : 0.5);
-                    const double bf = floor(r);
-                    const TW fr = (TW)(r - bf);
-                    const TW sq = sqrt(TW(1) + TW(4) * fr * (TW(1) - fr));
-                    w[e][0] = (TW(3) - TW(2) * fr - sq) * TW(0.125);
-                    w[e][1] = (TW(3) - TW(2) * fr + sq) * TW(0.125);
-                    w[e][2] = (TW(1) + TW(2) * fr + sq) * TW(0.125);
-                    w[e][3] = (TW(1) + TW(2) * fr - sq) * TW(0.125);
-                    // stencil start relative to the node's cell is -1 or -2
-                    const int ds = (int)bf - 1 - (int)floor(xs[e]);
-                    ls[e] = cw[e] - tb[e] + 2 + ds;
-                }
-                const TW* bd = box + d * E3;
-                TW acc = TW(0);
-                for (int c = 0; c < 4; ++c)
-                    for (int b = 0; b < 4; ++b) {
-                        const TW wyz = w[1][b] * w[2][c];
-                        const int row = ls[0] + E * ((ls[1] + b) + E * (ls[2] + c));
-                        for (int a = 0; a < 4; ++a) acc += bd[row + a] * (w[0][a] * wyz);
+        const auto nodes = [&](auto lanes) {
+            constexpr int L = decltype(lanes)::value;
+            for (int i = threadIdx.x / L; i < cnt; i += kSpreadChunk / L) {
+                const int q = perm[first + i], c0 = threadIdx.x % L;
+                const double X0 = X[3 * q], X1 = X[3 * q + 1], X2 = X[3 * q + 2];
+                const double xs[3] = {safe_coord(X0 * inv_h), safe_coord(X1 * inv_h), safe_coord(X2 * inv_h)};
+                int cw[3];
+                for (int e = 0; e < 3; ++e) cw[e] = wrap_mod((int)floor(xs[e]), n);
+                TW Uq[3];
+                for (int d = 0; d < 3; ++d) {
+                    int ls[3];
+                    TW w[3][4];
+                    for (int e = 0; e < 3; ++e) {
+                        const double r = xs[e] - (e == d ? 0.0 : 0.5);
+                        const double bf = floor(r);
+                        const TW fr = (TW)(r - bf);
+                        const TW sq = sqrt(TW(1) + TW(4) * fr * (TW(1) - fr));
+                        w[e][0] = (TW(3) - TW(2) * fr - sq) * TW(0.125);
+                        w[e][1] = (TW(3) - TW(2) * fr + sq) * TW(0.125);
+                        w[e][2] = (TW(1) + TW(2) * fr + sq) * TW(0.125);
+                        w[e][3] = (TW(1) + TW(2) * fr - sq) * TW(0.125);
+                        // stencil start relative to the node's cell is -1 or -2
+                        const int ds = (int)bf - 1 - (int)floor(xs[e]);
+                        ls[e] = cw[e] - tb[e] + 2 + ds;
                     }
-                Uq[d] = acc;
+                    const TW* bd = box + d * E3;
+                    TW acc = TW(0);
+    #pragma unroll
+                    for (int t = 0; t < 4 / L; ++t) {
+                        const int c = L == 1 ? t : c0;
+                        const TW wz = L == 1 ? w[2][t] : c == 0 ? w[2][0] : c == 1 ? w[2][1] : c == 2 ? w[2][2] : w[2][3];
+                        for (int b = 0; b < 4; ++b) {
+                            const TW wyz = w[1][b] * wz;
+                            const int row = ls[0] + E * ((ls[1] + b) + E * (ls[2] + c));
+                            for (int a = 0; a < 4; ++a) acc += bd[row + a] * (w[0][a] * wyz);
+                        }
+                    }
+                    for (int o = 1; o < L; o <<= 1) acc += __shfl_xor(acc, o, 64);   // (a node's lanes stay together)
+                    Uq[d] = acc;
+                }
+                if (c0 != 0) continue;
+                if (U) {
+                    U[3 * q] = (double)Uq[0];
+                    U[3 * q + 1] = (double)Uq[1];
+                    U[3 * q + 2] = (double)Uq[2];
+                }
+                if (Xupd) {
+                    Xupd[3 * q] = X0 + dt * (double)Uq[0];
+                    Xupd[3 * q + 1] = X1 + dt * (double)Uq[1];
+                    Xupd[3 * q + 2] = X2 + dt * (double)Uq[2];
+                }
             }
-            if (U) {
-                U[3 * q] = (double)Uq[0];
-                U[3 * q + 1] = (double)Uq[1];
-                U[3 * q + 2] = (double)Uq[2];
-            }
-            if (Xupd) {
-                Xupd[3 * q] = X0 + dt * (double)Uq[0];
-                Xupd[3 * q + 1] = X1 + dt * (double)Uq[1];
-                Xupd[3 * q + 2] = X2 + dt * (double)Uq[2];
-            }
-        }
+        };
+        if (sizeof(TW) == 8 && cnt <= kSpreadChunk / 4) nodes(std::integral_constant<int, 4>{});
+        else nodes(std::integral_constant<int, 1>{});
     }
 }
 
@@ -330,7 +397,7 @@ hipib_status launch_spread(hipib_ctx* ctx, const double* X, const double* F, dou
     if (ctx->cfg.deterministic) return det_spread(ctx, X, F, f, f_packed);
     const double h = ctx->h;
     const int64_t cap = spread_list_cap(ctx->ntiles, ctx->nn);
-    const int blocks = (int)(cap < 8192 ? cap : 8192);
+    const int blocks = (int)std::min(cap, kTileBlocks);
     const bool mixed = ctx->cfg.precision == HIPIB_MIXED;
 #define HIPIB_SPREAD(TT, TW)                                                                       \
     HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_SPREAD, 0.0, k_spread_tiles<TT, TW>, dim3(blocks, 3), dim3(kSpreadChunk), 0,  \
@@ -351,7 +418,7 @@ hipib_status launch_interpolate(hipib_ctx* ctx, const double* X, const double* u
                                 double* Xupd, double dt) {
     if (ctx->nn == 0) return HIPIB_OK;
     const int64_t cap = spread_list_cap(ctx->ntiles, ctx->nn);
-    const int blocks = (int)(cap < 8192 ? cap : 8192);
+    const int blocks = (int)std::min(cap, kTileBlocks);
     const bool mixed = ctx->cfg.precision == HIPIB_MIXED;
 #define HIPIB_INTERP(TT, TW)                                                                               \
     return launch_k(ctx, HIPIB_TIMER_INTERP, 0.0, k_interp_tiles<TT, TW>, dim3(blocks), dim3(kSpreadChunk), 0, X, \
@@ -454,7 +521,7 @@ hipib_status hipib_spread_noalloc(int32_t n, int32_t n_nodes, const double* X, c
     k_bin_count<<<nb, 256, 0, st>>>(X, n_nodes, n, T, ta, 1.0 / h, node_tile, node_rank, count, nullptr);
     k_bin_scan<<<1, 1024, 0, st>>>(count, ntiles, off, list, nlist, nullptr);
     k_bin_scatter<<<nb, 256, 0, st>>>(node_tile, node_rank, off, perm, n_nodes);
-    const int blocks = (int)(cap < 8192 ? cap : 8192);
+    const int blocks = (int)std::min(cap, kTileBlocks);
     const int64_t n3 = (int64_t)n * n * n;
     if (T == 8)
         k_spread_tiles<8, double><<<dim3(blocks, 3), kSpreadChunk, 0, st>>>(X, F, f, perm, off, list, nlist, n, ta,
