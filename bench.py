@@ -251,7 +251,7 @@ def kernel_classes(hipib):
          "spreading: 52 B/node (X, F, order) + 16 B per touched grid value (f read and written)"),
         (H.TIMER_INTERP, "k_interp_tiles<8,double>",
          "interpolation and position update: 52 B/node (X read and written, order) + 8 B per touched grid value"),
-        (H.TIMER_FE_FORCE, "k_fe_force<double,Hex8>", "element forces, 3.7 kflop per hex (FP64 ALU)"),
+        (H.TIMER_FE_FORCE, "k_hex_force", "element forces, 3.7 kflop per hex (FP64 ALU)"),
     ]
 
 
@@ -314,11 +314,11 @@ def roofline_table(hipib, tim, classes, steps, nodes_bytes, fe_flops):
     return dict(sorted(rows.items(), key=lambda kv: -kv[1]["ms_per_step"]))
 
 
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2503_22695_amd", "csrc", "mg.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2503_22695_amd", "csrc", f) for f in ("mg.hip", "mg_march.h")]
 
 
 # kernel classes with a committed counter summary: profiles/<prefix>_<workload>_hbm_traffic.md
-TRAFFIC_PROFILES = {"k_gs<double,2>": "k_gs_poisson_fine", "k_gs<double,1,true>": "k_gs_helmholtz_sor_fine"}
+TRAFFIC_PROFILES = {"k_march<double,up,dots>": "k_march_up_dots", "k_march<double,relax>": "k_march_relax"}
 
 
 def measured_traffic(kernel_class: str, workload: str = "128"):
@@ -344,16 +344,17 @@ def measured_traffic(kernel_class: str, workload: str = "128"):
 
 
 def kernel_code_sha256(path: str = None) -> str:
-    """sha256 of the multigrid source without its // comments, trailing blanks
+    """sha256 of the multigrid sources without their // comments, trailing blanks
     and empty lines: the code the counters were taken on (comment edits do not
     change it)."""
     import hashlib
     import re
     lines = []
-    for ln in open(path or KERNEL_SOURCE, encoding="utf-8").read().splitlines():
-        ln = re.sub(r"//.*$", "", ln).rstrip()
-        if ln:
-            lines.append(ln)
+    for source in [path] if path else KERNEL_SOURCES:
+        for ln in open(source, encoding="utf-8").read().splitlines():
+            ln = re.sub(r"//.*$", "", ln).rstrip()
+            if ln:
+                lines.append(ln)
     return hashlib.sha256("\n".join(lines).encode()).hexdigest()
 
 
@@ -517,8 +518,8 @@ def main():
                                "(one solver field 56.6 MB: the solve's arrays exceed the 256 MB last-level cache)",
                    "kernels": roofline_table(hipib, tim192, sub, 5, nb192, FE_FLOP_PER_HEX * lprob.n_elems),
                    "stencil_footprint_values": fp192}
-        if "k_gs<double,2>" in roof192["kernels"]:
-            roof192["kernels"]["k_gs<double,2>"]["traffic"] = measured_traffic("k_gs<double,2>", "192")
+        if "k_march<double,up,dots>" in roof192["kernels"]:
+            roof192["kernels"]["k_march<double,up,dots>"]["traffic"] = measured_traffic("k_march<double,up,dots>", "192")
         del lsim
         progress("192^3 leg done")
 
