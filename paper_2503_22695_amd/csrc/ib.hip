@@ -279,8 +279,11 @@ k_spread_tiles(const double* __restrict__ X, const double* __restrict__ F, doubl
 // nodes: four threads to a node, one plane of its stencils each, so that the sums of
 // a sparse item are a quarter as long (216 elements at 32^3: 14.6 -> 6.7 us, 126000
 // nodes at 128^3 30.6 -> 26.0, 281000 at 192^3 53.6 -> 40.7; four threads for every item
-// 31.4 at 128^3).  In FP32 one thread sums in the order of a direct gather, which
-// FP32 results depend on.  TW: type of the box, the weights and the accumulation.
+// 31.4 at 128^3).  In FP64 a node's sum has one order wherever it lands: each plane
+// in the order of a direct gather, then (0 + 1) + (2 + 3), by one thread or by four.
+// Which nodes share an item depends on the order of the binning's atomics.  In FP32
+// one thread sums in the order of a direct gather, which FP32 results depend on.
+// TW: type of the box, the weights and the accumulation.
 template <int T, typename TW>
 __global__ void __launch_bounds__(kSpreadChunk)
 k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict__ U, double* Xupd, double dt,
@@ -316,6 +319,7 @@ k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict
                 for (int d = 0; d < 3; ++d) box[d * E3 + e] = v[r][d];
         }
         __syncthreads();
+        constexpr bool planes = sizeof(TW) == 8;
         const auto nodes = [&](auto lanes) {
             constexpr int L = decltype(lanes)::value;
             for (int i = threadIdx.x / L; i < cnt; i += kSpreadChunk / L) {
@@ -342,9 +346,10 @@ k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict
                         ls[e] = cw[e] - tb[e] + 2 + ds;
                     }
                     const TW* bd = box + d * E3;
-                    TW acc = TW(0);
+                    TW acc = TW(0), plane[4 / L];
     #pragma unroll
                     for (int t = 0; t < 4 / L; ++t) {
+                        if (planes) acc = TW(0);
                         const int c = L == 1 ? t : c0;
                         const TW wz = L == 1 ? w[2][t] : c == 0 ? w[2][0] : c == 1 ? w[2][1] : c == 2 ? w[2][2] : w[2][3];
                         for (int b = 0; b < 4; ++b) {
@@ -352,7 +357,9 @@ k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict
                             const int row = ls[0] + E * ((ls[1] + b) + E * (ls[2] + c));
                             for (int a = 0; a < 4; ++a) acc += bd[row + a] * (w[0][a] * wyz);
                         }
+                        plane[t] = acc;
                     }
+                    if constexpr (L == 1 && planes) acc = (plane[0] + plane[1]) + (plane[2] + plane[3]);
                     for (int o = 1; o < L; o <<= 1) acc += __shfl_xor(acc, o, 64);   // (a node's lanes stay together)
                     Uq[d] = acc;
                 }
@@ -369,8 +376,12 @@ k_interp_tiles(const double* X, const double* __restrict__ u, double* __restrict
                 }
             }
         };
-        if (sizeof(TW) == 8 && cnt <= kSpreadChunk / 4) nodes(std::integral_constant<int, 4>{});
-        else nodes(std::integral_constant<int, 1>{});
+        bool four = false;
+        if constexpr (planes) {
+            four = cnt <= kSpreadChunk / 4;
+            if (four) nodes(std::integral_constant<int, 4>{});
+        }
+        if (!four) nodes(std::integral_constant<int, 1>{});
     }
 }
 

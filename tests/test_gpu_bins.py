@@ -47,3 +47,25 @@ def test_bins(torch_dev, hp, ref, n, even, crowd, det):
         ctx.spread(Xd, to_dev(torch, F), f)
         assert_close("f", host(f), ref.spread(n, X, F))
         assert_close("U", host(ctx.interpolate(Xd, to_dev(torch, u))), ref.interpolate(X, u))
+
+
+@pytest.mark.parametrize("n,mixed,det", [(64, 0, 0), (64, 0, 1), (12, 0, 0), (64, 1, 0)])
+def test_interpolation_order(torch_dev, hp, n, mixed, det):
+    """A node's interpolated velocity has the same bits whatever the order of the
+    nodes and whichever others share its tile: a tile of 300 nodes (a full work
+    item and one of 44), sparse tiles, several orders, and part of the nodes
+    alone, so that the crowded tile is sparse."""
+    torch = torch_dev
+    say("interpolation order", n, mixed, det)
+    rng = np.random.default_rng(17 + n)
+    X = np.concatenate([rng.uniform(-0.3, 1.3, (400, 3)), rng.uniform(0.05, 0.05 + 2.0 / n, (300, 3))])
+    u = to_dev(torch, rng.standard_normal((3, n, n, n)))
+
+    def interpolate(nodes):
+        ctx = plain_ctx(hp, n, deterministic=det, precision=hp.MIXED if mixed else hp.FP64)
+        ctx.set_mesh(X[nodes], np.zeros((0, 8)), np.zeros((0, 3)), np.zeros(0))
+        return host(ctx.interpolate(to_dev(torch, X[nodes]), u))
+
+    U = interpolate(np.arange(len(X)))
+    for nodes in [rng.permutation(len(X)) for _ in range(4)] + [np.arange(len(X))[::-1], np.arange(0, len(X), 7)]:
+        assert np.array_equal(interpolate(nodes), U[nodes])
