@@ -904,12 +904,12 @@ k_cg_dir(const TZ* __restrict__ z, double* __restrict__ p, double* __restrict__ 
     }
 }
 
-// The end of the enqueued iterations: alpha = (r.z) / (p.q), p.q summed from the
-// npq partials of k_cg_dir in a fixed order by every block (so all blocks hold
-// the same alpha; block 0 keeps it in the state for the next beta); then
-// x += alpha p, r -= alpha q, partials of ||r||^2 (part[block]) and of sum x
-// (part[gridDim.x + block], for the mean of the converged solution); r32 (mixed)
-// = r / ||b||.  Where an iteration before has stopped, only its step of x is due.
+// The step of an iteration whose next one does not take it (cg_fuses): alpha =
+// (r.z) / (p.q), p.q summed from the npq partials of k_cg_dir in a fixed order by
+// every block (so all blocks hold the same alpha; block 0 keeps it in the state for
+// the next beta); then x += alpha p, r -= alpha q, partials of ||r||^2 (part[block])
+// and of sum x (part[gridDim.x + block], for the mean of the converged solution);
+// r32 (mixed) = r / ||b||.
 constexpr int kUpdThreads = 512, kUpdMaxBlocks = 512;   // (256 x 1024: 22.1 us at 128^3; 512 x 512: 19.7)
 __global__ void __launch_bounds__(kUpdThreads)
 k_cg_update(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
@@ -917,19 +917,7 @@ k_cg_update(double* __restrict__ x, double* __restrict__ r, const double* __rest
             float* __restrict__ r32, const double* __restrict__ pq_part, int npq, double* __restrict__ part) {
     __shared__ double red[16];
     const int64_t stride = (int64_t)gridDim.x * kUpdThreads;
-    if (!st->active[0]) {  // uniform
-        if (!st->x_pending) return;
-        const double alpha = st->alpha;
-        double sx = 0.0;
-        for (int64_t t = (int64_t)blockIdx.x * kUpdThreads + threadIdx.x; t < n3; t += stride) {
-            const double xn = x[t] + alpha * p[t];
-            x[t] = xn;
-            sx += xn;
-        }
-        sx = block_sum(sx, red);
-        if (threadIdx.x == 0) part[gridDim.x + blockIdx.x] = sx;
-        return;
-    }
+    if (!st->active[0]) return;  // uniform
     const double alpha = cg_alpha(pq_part, npq, st->rz[slot], red), inv_bn = r32 ? 1.0 / st->bn[0] : 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) st->alpha = alpha;
     double v = 0.0, sx = 0.0;
@@ -964,6 +952,86 @@ k_cg_update(double* __restrict__ x, double* __restrict__ r, const double* __rest
     if (threadIdx.x == 0) {
         part[blockIdx.x] = v;
         part[gridDim.x + blockIdx.x] = sx;
+    }
+}
+
+// The same at the end of a batch of iterations where the others leave their steps to
+// the passes that follow them (cg_fuses).  ||r||^2 is summed by the boxes of the down
+// half in the order of its threads (a column's red cells, its black cells, their sum,
+// the workgroup's threads), so that norm and stop test do not depend on the batches an
+// iteration was enqueued in; a thread takes one colour of a column, four planes of it in
+// flight (eight: no faster).  20.3 us at 128^3 where k_cg_update takes 18.6 (4.9 TB/s),
+// and a pass that sums r again by boxes after it 6.4 more.  Where an iteration before
+// has stopped, only its step of x is due.
+__global__ void __launch_bounds__(kUpdThreads)
+k_cg_close(double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
+           const double* __restrict__ q, int n, MarchBox box, unsigned nboxes, MGState* __restrict__ st, int slot,
+           float* __restrict__ r32, const double* __restrict__ pq_part, int npq, double* __restrict__ part) {
+    constexpr int DH = march_halo(3, MARCH_RESTRICT);
+    __shared__ double red[16], sq[2 * kMarchThreads];
+    const unsigned blk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);   // (as k_march)
+    const bool step = st->active[0];
+    if (blk >= nboxes || (!step && !st->x_pending)) return;   // uniform
+    const int tid = threadIdx.x, H = n >> 1;
+    const int x0 = blk % box.ntx * box.XO, j0 = blk / box.ntx % box.nty * box.JO, k0 = blk / (box.ntx * box.nty) * box.ZO;
+    const int xo = min(box.XO, H - x0), jo = min(box.JO, n - j0), zo = min(box.ZO, n - k0), C = xo * jo;
+    const int64_t pst = (int64_t)H * n;
+    const double alpha = step ? cg_alpha(pq_part, npq, st->rz[slot], red) : st->alpha;
+    const double inv_bn = r32 ? 1.0 / st->bn[0] : 0.0;
+    if (step && blk == 0 && tid == 0) st->alpha = alpha;
+    double sx = 0.0;
+    for (int item = tid; item < 2 * C; item += kUpdThreads) {
+        const int black = item >= C, col = black ? item - C : item, ly = col / xo;
+        const int64_t o = (black ? pst * n : 0) + pst * k0 + (int64_t)H * (j0 + ly) + x0 + col - ly * xo;
+        double v = 0.0;
+        for (int z0 = 0; z0 < zo; z0 += 4) {
+            double xv[4], rv[4], pv[4], qv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t t = o + pst * (z0 + u);
+                if (z0 + u < zo) {
+                    xv[u] = x[t];
+                    pv[u] = p[t];
+                    if (step) {
+                        rv[u] = r[t];
+                        qv[u] = q[t];
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t t = o + pst * (z0 + u);
+                if (z0 + u < zo) {
+                    const double xn = xv[u] + alpha * pv[u];
+                    x[t] = xn;
+                    sx += xn;
+                    if (step) {
+                        const double rn = rv[u] - alpha * qv[u];
+                        r[t] = rn;
+                        v = fma(rn, rn, v);
+                        if (r32) r32[t] = (float)(rn * inv_bn);
+                    }
+                }
+            }
+        }
+        sq[item] = v;
+    }
+    sx = block_sum(sx, red);   // (and sq is written)
+    if (tid == 0) part[nboxes + blk] = sx;
+    if (!step) return;
+    const int nw = box.threads >> 6;
+    for (int w = tid >> 6; w < nw; w += kUpdThreads / 64) {
+        const int t = 64 * w + (tid & 63), row = t / box.W, ly = row - DH, lx = t - row * box.W - box.HX;
+        const int col = ly * xo + lx;
+        double v = ly >= 0 && ly < jo && lx >= 0 && lx < xo ? sq[col] + sq[C + col] : 0.0;
+        for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s, 64);
+        if ((tid & 63) == 0) red[w] = v;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double v = 0.0;
+        for (int w = 0; w < nw; ++w) v += red[w];
+        part[blk] = v;
     }
 }
 
@@ -1079,6 +1147,23 @@ __device__ __forceinline__ void stop_decision(MGState* st, int comp, int mode, d
     }
     st->active[comp] = act;
     if (mode == FIN_CG_STEP && !act) st->x_pending = 1;
+}
+
+// The sum of np partials on thread 0 of a workgroup of whole wavefronts, in the order
+// of k_finalize's 1024 threads whatever the workgroup.
+__device__ __forceinline__ double finalize_sum(const double* __restrict__ part, int np, double* red /*[16]*/) {
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    for (int w = threadIdx.x >> 6; w < 16; w += nw) {
+        double s = 0.0;
+        for (int t = 64 * w + lane; t < np; t += 1024) s += part[t];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (lane == 0) red[w] = s;
+    }
+    __syncthreads();
+    double s = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < 16; ++w) s += red[w];
+    return s;
 }
 
 // Reduce the partials of each component (fixed order) and update the state.
@@ -1345,9 +1430,7 @@ k_exact_fwd_xy(const T* __restrict__ bg, int64_t cs, const T* __restrict__ tab, 
         if (blockIdx.x == N) {
             __shared__ double red[16];
             if (!stop.st->active[0]) return;   // uniform
-            double s = 0.0;
-            for (int t = threadIdx.x; t < stop.nparts; t += kPlaneThreads) s += stop.part[t];
-            s = block_sum(s, red);
+            const double s = finalize_sum(stop.part, stop.nparts, red);
             if (threadIdx.x == 0)
                 stop_decision(stop.st, 0, stop.mode, sqrt(s), stop.rtol, stop.max_cycles, stop.fixed_cycles);
             return;
@@ -1744,12 +1827,6 @@ int sum_blocks(int64_t count) {
     return (int)(b < 1024 ? (b < 1 ? 1 : b) : 1024);
 }
 
-// workgroups of the conjugate-gradient update pass
-int update_blocks(int64_t count) {
-    int64_t b = (count + kUpdThreads - 1) / kUpdThreads;
-    return (int)(b < kUpdMaxBlocks ? (b < 1 ? 1 : b) : kUpdMaxBlocks);
-}
-
 struct OpCoef {
     double sigma, nu;
     int poisson;
@@ -1824,7 +1901,8 @@ double* state_field(const hipib_ctx* ctx, size_t offset) {
 }
 
 // partials of conjugate gradients: the dots first (at most twice 2 norm_parts of
-// each), then p.q (norm_parts), then ||r||^2 and sum x
+// each), then p.q (norm_parts), then ||r||^2 and sum x (cg_fuses: by boxes, of at
+// least 16 packed columns x 4 x 4, so at most 4096 of them at n <= 160)
 int64_t cg_pq_offset(int n) { return 4 * norm_parts(n); }
 int64_t cg_norm_offset(int n) { return cg_pq_offset(n) + norm_parts(n); }
 
@@ -1993,16 +2071,24 @@ MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots,
     return best;
 }
 
-// Launches a fused pass; pass: the slot of its box in the context (the boxes
-// depend on the level, the components and the pass only).
+// The box of a fused pass, kept in the context: boxes depend on the level, the
+// components and the pass only.
+template <int SRC, int NS, int RES, typename T>
+const MarchBox* pass_box(hipib_ctx* ctx, int l, int ncomp) {
+    constexpr int halo = march_halo(NS, RES), lead = march_lead(SRC, NS, RES) - halo;
+    MarchBox& box = ctx->march_box[l][ncomp - 1][4 * SRC + RES];
+    if (box.XO == 0)
+        box = march_box(ctx->lv[l].n, ncomp, halo, march_halo_x(SRC, NS, RES), lead + march_extra(RES),
+                        march_slots(SRC, NS, RES), (int)sizeof(T));
+    return &box;
+}
+
+// Launches a fused pass.
 template <int SRC, int NS, bool SOR, int RES, bool CG = false, typename T>
 hipib_status march(hipib_ctx* ctx, int l, int kind, double bytes, const MarchArgs<T>& args, int ncomp,
                    int64_t* blocks = nullptr, std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A = {}) {
     static_cast<MarchArgs<T>&>(A) = args;
-    constexpr int halo = march_halo(NS, RES), halo_x = march_halo_x(SRC, NS, RES), slots = march_slots(SRC, NS, RES), lead = march_lead(SRC, NS, RES) - halo;
-    constexpr int pass = 4 * SRC + RES;
-    MarchBox& box = ctx->march_box[l][ncomp - 1][pass];
-    if (box.XO == 0) box = march_box(A.n, ncomp, halo, halo_x, lead + march_extra(RES), slots, (int)sizeof(T));
+    const MarchBox& box = *pass_box<SRC, NS, RES, T>(ctx, l, ncomp);
     if (box.XO == 0) return fail(HIPIB_E_INVAL, "fused pass: no box for n = %d", A.n);
     A.box = box;
     A.st = ctx->st;
@@ -2307,12 +2393,28 @@ bool cg_fuses(const hipib_ctx* ctx) {
            5.0 * sizeof(double) * (double)ctx->n3 <= 160e6;
 }
 
+// the boxes of the down half that takes the step of r
+MarchBox cg_box(hipib_ctx* ctx) {
+    return ctx->cfg.precision == HIPIB_MIXED ? *pass_box<MARCH_ZERO, 3, MARCH_RESTRICT, float>(ctx, 0, 1)
+                                             : *pass_box<MARCH_ZERO, 3, MARCH_RESTRICT, double>(ctx, 0, 1);
+}
+
+// workgroups of the pass that ends a batch of iterations
+int update_blocks(hipib_ctx* ctx) {
+    if (cg_fuses(ctx)) {
+        const MarchBox box = cg_box(ctx);
+        return box.ntx * box.nty * box.ntz;
+    }
+    return (int)std::min<int64_t>((ctx->n3 + kUpdThreads - 1) / kUpdThreads, kUpdMaxBlocks);
+}
+
 // One preconditioned conjugate-gradient iteration of the Poisson solve, number
-// it of the solve.  An iteration's step of r and its stop test are left to the
-// finest-level down half of the next iteration (which then reads r and q
-// instead of r) and its step of x to the next k_cg_dir, when the next one is
-// enqueued with it and cg_fuses; `last` ends the batch with k_cg_update, `follows`
-// says that the iteration before was left open.
+// it of the solve.  Where cg_fuses, an iteration that another one follows in its batch
+// leaves its step of r and its stop test to the finest-level down half of the next
+// (which then reads r and q instead of r) and its step of x to the next k_cg_dir;
+// `last` ends the batch with k_cg_close, `follows` says that the iteration before was
+// left open.  Either way x, r and ||r|| have the same bits: what a solve returns does
+// not depend on the batches it was enqueued in.
 hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc, int it, bool follows, bool last) {
     const int n = ctx->n;
     const int64_t n3 = ctx->n3;
@@ -2363,11 +2465,17 @@ hipib_status cg_iteration(hipib_ctx* ctx, const OpCoef& oc, int it, bool follows
                         oc.sigma, c, ctx->st, ctx->part, dparts, dparts, first, slot, pq);
     };
     HIPIB_TRY(mixed ? dir(ctx->e32) : dir(z));
-    if (!last && cg_fuses(ctx)) return HIPIB_OK;
-    const int nbu = update_blocks(n3);
-    HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_UPDATE, (mixed ? 52.0 : 48.0) * n3, k_cg_update, dim3(nbu), dim3(kUpdThreads), 0,
-                       ctx->sx, r, p, q, n3, ctx->st, slot, mixed ? ctx->r32 : nullptr, pq, npq,
-                       ctx->part + cg_norm_offset(n)));
+    if (!last && fuses) return HIPIB_OK;
+    const double ubytes = (mixed ? 52.0 : 48.0) * (double)n3;
+    float* const r32 = mixed ? ctx->r32 : nullptr;
+    double* const part = ctx->part + cg_norm_offset(n);
+    const int nbu = update_blocks(ctx);
+    if (fuses)
+        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_UPDATE, ubytes, k_cg_close, dim3((nbu + 7) / 8 * 8), dim3(kUpdThreads), 0,
+                           ctx->sx, r, p, q, n, cg_box(ctx), (unsigned)nbu, ctx->st, slot, r32, pq, npq, part));
+    else
+        HIPIB_TRY(launch_k(ctx, HIPIB_TIMER_CG_UPDATE, ubytes, k_cg_update, dim3(nbu), dim3(kUpdThreads), 0, ctx->sx, r, p,
+                           q, n3, ctx->st, slot, r32, pq, npq, part));
     if (!last) return leave_stop_test(ctx, nbu, FIN_CYCLE_R);
     return finalize_at(ctx, cg_norm_offset(n), nbu, nbu, 1, FIN_CYCLE_R, 0.0);
 }
@@ -2576,9 +2684,9 @@ hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b
     }
     *mean_ok = oc.poisson && ctx->st_host->status == HIPIB_OK;
     if (*mean_ok && cg && ctx->st_host->cycles[0] > 0) {
-        // the k_cg_update of the last batch that did not start converged left the
-        // partial sums of x after its ||r||^2 partials
-        const int nbu = update_blocks(ctx->n3);
+        // the end of the last batch that did not start converged left the partial
+        // sums of x after its ||r||^2 partials
+        const int nbu = update_blocks(ctx);
         HIPIB_TRY(finalize_at(ctx, cg_norm_offset(ctx->n) + nbu, nbu, nbu, 1, FIN_MEAN_ALL, 1.0 / (double)ctx->n3));
     } else if (*mean_ok) {
         k_sum_partials<<<dim3(nb, ncomp), 256, 0, ctx->stream>>>(xpk, ctx->n3, ctx->n3, 0, nullptr, ctx->part,

@@ -138,7 +138,7 @@ __device__ __forceinline__ void put_byte(T* base, int64_t o, uint32_t lane, T v)
 // alpha = rz / (sum of the npq partials of p.q), for every thread of a workgroup of
 // whole wavefronts; red: 8 doubles of LDS, free again on return.  The order of the
 // sum is that of 512 threads whatever the workgroup, so that a step taken by
-// k_cg_update and one taken by a down half are the same to the bit.
+// k_cg_close and one taken by a down half are the same to the bit.
 __device__ __forceinline__ double cg_alpha(const double* __restrict__ pq, int npq, double rz, double* red) {
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     for (int w = threadIdx.x >> 6; w < 8; w += nw) {
@@ -186,7 +186,7 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
     static_assert(PF == 4, "the coarse rows are read ahead two coarse planes");
     extern __shared__ unsigned char march_lds[];
     T* const L = reinterpret_cast<T*>(march_lds);
-    const int n = A.n, H = n >> 1, W = A.box.W, tid = threadIdx.x, nt = blockDim.x;
+    const int n = A.n, H = n >> 1, W = A.box.W, tid = threadIdx.x;
     // each XCD takes a contiguous eighth of the boxes (see xcd_block; the grid is the
     // boxes rounded up to a multiple of 8)
     const unsigned blk = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
@@ -392,7 +392,9 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
         }
     };
 
-    // ||b - A x||^2 (CG: ||r||^2) over the box: the residual of the colour relaxed last is
+    // CG: ||r||^2 over the box by colour (k_cg_close sums in the same order)
+    double rc[2] = {0.0, 0.0};
+    // ||b - A x||^2 over the box: the residual of the colour relaxed last is
     // diag (1 - omega) / omega times its last change (none without over-relaxation)
     double rn = 0.0;
     const T wl = (T(1) / A.inv_diag) * (T(1) - A.omega) / A.omega;
@@ -429,7 +431,7 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
                     bh[q][q ? FB : FR] = sizeof(T) == 4 ? (T)(r * inv_bn) : (T)r;
                     const int P = z - (q ? FB : FR);
                     if (P >= k0 && P < k0 + zo && own) {
-                        rn += r * r;
+                        rc[q] = fma(r, r, rc[q]);
                         put_byte(A.rnew + q * half3, D8 * (P * pby), D8 * goff, r);
                         if (sizeof(T) == 4) put_byte(A.b32 + q * half3, P * pby, goff, (float)(r * inv_bn));
                     }
@@ -514,25 +516,10 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
         }
     }
     if constexpr (RES == MARCH_DOTS || RES == MARCH_NORM || CG) {
-        if (RES != MARCH_DOTS) da = rn;
-        if (CG) __syncthreads();             // (the restriction after the last barrier read LDS)
         double* const red = reinterpret_cast<double*>(march_lds);   // (the last barrier is behind every read)
-        for (int o = 32; o > 0; o >>= 1) {
-            da += __shfl_down(da, o, 64);
-            if (RES == MARCH_DOTS) dd += __shfl_down(dd, o, 64);
-        }
-        const int nw = nt >> 6;
-        if ((tid & 63) == 0) {
-            red[tid >> 6] = da;
-            red[nw + (tid >> 6)] = dd;
-        }
-        __syncthreads();
+        const double sa = block_sum(RES == MARCH_DOTS ? da : CG ? rc[0] + rc[1] : rn, red);
+        const double sd = RES == MARCH_DOTS ? block_sum(dd, red) : 0.0;
         if (tid == 0) {
-            double sa = 0.0, sd = 0.0;
-            for (int w = 0; w < nw; ++w) {
-                sa += red[w];
-                sd += red[nw + w];
-            }
             if (RES == MARCH_DOTS) {
                 A.part[blk] = sa;
                 A.part[A.pstride + blk] = sd;

@@ -105,3 +105,38 @@ def test_open_iterations_bitwise(torch_dev, hp, n, mixed):
     for one, other in (("first", "again"), ("first", "short"), ("easy", "easy after")):
         assert out[one][0] == out[other][0]
         assert np.array_equal(out[one][1], out[other][1]), (one, other)
+
+
+@pytest.mark.parametrize("n,mixed,over", [
+    (48, 0, {}), (64, 0, {}), (96, 1, {}), (128, 0, {}), (192, 0, {}),
+    (32, 0, {"mg_coarse_sweeps": 4}), (64, 0, {"mg_coarse_sweeps": 4}), (96, 1, {"mg_coarse_sweeps": 4}),
+    (48, 0, {"mg_pre": 1, "mg_post": 1}), (24, 0, {}),
+    (64, 0, {"mg_fixed_cycles": 3}), (64, 0, {"mg_max_cycles": 3}), (96, 1, {"mg_max_cycles": 3}),
+    (64, 0, {"mg_max_cycles": 3, "mg_coarse_sweeps": 4})])
+def test_batches_return_the_same(torch_dev, hp, n, mixed, over):
+    """What a conjugate-gradient solve returns (solution, cycles, residual norm, or
+    that it did not converge) has the same bits however its iterations were
+    enqueued: one at a time in a context's first solve, all together after a
+    like one, in a batch too short after an easier one, too long after a harder one (it
+    stops at an iteration that others follow); exact and relaxed coarsest levels,
+    stops by the tolerance, by a fixed number of cycles and by the limit."""
+    torch = torch_dev
+    say("batches", n, mixed, over)
+    rng = np.random.default_rng(3 * n)
+    b = rng.standard_normal((n, n, n))
+    b -= b.mean()
+    easy = np.cos(2 * np.pi * np.arange(n) / n) * np.ones((n, n, 1))   # an eigenvector: few iterations
+    ctx = plain_ctx(hp, n, precision=hp.MIXED if mixed else hp.FP64, **over)
+    out = []
+    for rhs in (easy, easy, b, b, easy):
+        x = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+        try:
+            cyc, rr = ctx.mg_solve(hp.OP_POISSON, to_dev(torch, rhs), x)
+            out.append((int(cyc[0]), float(rr[0]), host(x)))
+        except hp.HipIBError as e:
+            assert over.get("mg_max_cycles") and e.status == 4   # HIPIB_E_NOCONV
+            out.append((-1, 0.0, host(x)))
+    say("cycles", [o[0] for o in out])
+    for one, other in ((0, 1), (0, 4), (2, 3)):
+        assert out[one][:2] == out[other][:2], (one, other, out[one][:2], out[other][:2])
+        assert np.array_equal(out[one][2], out[other][2]), (one, other)
