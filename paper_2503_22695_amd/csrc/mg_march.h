@@ -367,9 +367,11 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
 
     // half-sweep s on plane z - s, all but the neighbour at k + 1: the in-plane sum
     // with the own values of half-sweep s - 1 at k and k - 1; old: of the cell itself
+    T s4 = T(0);                             // (MARCH_NORM: its four neighbours in half-sweep 4)
     auto partial = [&](int s, int zpar, T own_k, T own_km, T old) {
         const int q = (q0 + s) & 1, ppar = (zpar + s) & 1, sl = 2 * (s - 1) + ppar;
         const T sn = (L[(((ppar + q) & 1) ? sO : sE) + sl] + own_k) + (L[up + sl] + L[dn + sl]) + own_km;
+        if (RES == MARCH_NORM && s == 4) s4 = ((L[(((ppar + q) & 1) ? sO : sE) + sl] + own_k) + L[up + sl]) + L[dn + sl];
         T v = wb * (bh[q][s] + A.c * sn);
         if (SOR && (s >= 2 || SRC == MARCH_GUESS)) v += wo * old;
         return v;
@@ -394,10 +396,15 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
 
     // CG: ||r||^2 over the box by colour (k_cg_close sums in the same order)
     double rc[2] = {0.0, 0.0};
-    // ||b - A x||^2 over the box: the residual of the colour relaxed last is
-    // diag (1 - omega) / omega times its last change (none without over-relaxation)
+    // ||b - A x||^2 over the box, both colours (the last half-sweep's neighbours are
+    // final, so its cells' residuals follow from what it read).  Where a tight
+    // tolerance stops, the norm is the rounding of A x: half of it is in each colour,
+    // and a sum of neighbours in the order in which the cell was relaxed would hide its
+    // part.  So the terms are those of k_resid_norm.
     double rn = 0.0;
-    const T wl = (T(1) / A.inv_diag) * (T(1) - A.omega) / A.omega;
+    auto residual = [&](T b, T x, T s4, T kp, T km) {
+        return b - (A.sigma * x - A.c * (((s4 + kp) + km) - T(6) * x));
+    };
 
     // A step runs the half-sweeps in three groups: the source and half-sweep 1, then
     // 2 and 3, then the rest.  Inside a group the code is straight-line: all in-plane
@@ -487,13 +494,19 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
                     const int ppar = (zpar + NS + 1) & 1;         // parity of the residual's plane
                     if constexpr (RESID) {
                         const T* const Lp = L + 2 * NS + ppar;
-                        const T sn = (Lp[((ppar + qr) & 1) ? sO : sE] + kr) + (Lp[up] + Lp[dn]) + mr;
-                        rpre = bh[qr][NS + 1] - (A.sigma * xv - A.c * (sn - T(6) * xv));
+                        const T side = Lp[((ppar + qr) & 1) ? sO : sE];
+                        if constexpr (RES == MARCH_NORM) {
+                            rpre = ((side + kr) + Lp[up]) + Lp[dn];
+                        } else {
+                            const T sn = (side + kr) + (Lp[up] + Lp[dn]) + mr;
+                            rpre = bh[qr][NS + 1] - (A.sigma * xv - A.c * (sn - T(6) * xv));
+                        }
                     }
                     if constexpr (RES == MARCH_RESTRICT) {
                         rside = L[EX + 1 - ppar + ((1 - ppar) ? sE : sO)];
                         if (coarse && z - NS - 3 >= k0 - 1) restrict_rows(z - NS - 3, ppar);
                     }
+                    const T v3 = v;                               // of half-sweep 3 at k + 1
                     if constexpr (NS >= 4) finish(4, z, u, zpar, pre4, v);
                     if constexpr (RES == MARCH_RESTRICT) {
                         // x sum of the residuals of plane z - NS - 2, then the red residuals of
@@ -505,9 +518,9 @@ k_march(std::conditional_t<CG, MarchCgArgs<T>, MarchArgs<T>> A) {
                     }
                     if constexpr (RES == MARCH_NORM) {
                         const int P = z - NS - 1;
-                        const T res = rpre + A.c * v, last = wl * (v - m2);
+                        const T res = residual(bh[qr][NS + 1], xv, rpre, v, mr), last = residual(bh[q0][4], v, s4, v3, m3);
                         if (own && P >= k0 && P < k0 + zo) rn += (double)res * (double)res;
-                        if (SOR && own && P + 1 >= k0 && P + 1 < k0 + zo) rn += (double)last * (double)last;
+                        if (own && P + 1 >= k0 && P + 1 < k0 + zo) rn += (double)last * (double)last;
                     }
                 }
             }

@@ -140,3 +140,27 @@ def test_batches_return_the_same(torch_dev, hp, n, mixed, over):
     for one, other in ((0, 1), (0, 4), (2, 3)):
         assert out[one][:2] == out[other][:2], (one, other, out[one][:2], out[other][:2])
         assert np.array_equal(out[one][2], out[other][2]), (one, other)
+
+
+@pytest.mark.parametrize("n,sigma", [(48, 0.1), (96, 0.1), (48, 1e4), (96, 645.12)])
+def test_norm_of_a_converged_cycle(torch_dev, hp, n, sigma):
+    """The residual norm that the last fused pass of a cycle sums, where x is as
+    converged as rounding lets it be, against that of the pass that starts a
+    solve (a second solve from x that has nothing to do): both colours' rounding
+    is in it.  Descending cycles (sigma = 0.1) and over-relaxed ones on the
+    finest level.
+
+    Both add the terms of the same formula.  With smooth data one colour's alone
+    give 0.67 to 0.71 of the norm (simulated in numpy, with and without fused
+    multiply-adds), and the rounding of another order of a cell's neighbours 0.93 to
+    1.01: the bound is half way."""
+    torch = torch_dev
+    say("norm of a converged cycle", n, sigma)
+    t = 2 * np.pi * np.arange(n) / n
+    b = np.cos(t)[:, None, None] * np.cos(2 * t)[:, None] + np.sin(t)
+    bd = to_dev(torch, b)
+    xd = torch.zeros((n, n, n), dtype=torch.float64, device="cuda")
+    _, last = plain_ctx(hp, n, dt=1.0 / sigma, mg_fixed_cycles=25).mg_solve(hp.OP_HELMHOLTZ, bd, xd)
+    cyc, start = plain_ctx(hp, n, dt=1.0 / sigma, mg_rtol=1e-6).mg_solve(hp.OP_HELMHOLTZ, bd, xd)
+    assert cyc[0] == 0
+    assert abs(last[0] / start[0] - 1.0) <= 0.15, (last[0], start[0])
