@@ -314,7 +314,7 @@ def roofline_table(hipib, tim, classes, steps, nodes_bytes, fe_flops):
     return dict(sorted(rows.items(), key=lambda kv: -kv[1]["ms_per_step"]))
 
 
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2503_22695_amd", "csrc", f) for f in ("mg.hip", "mg_march.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2503_22695_amd", "csrc", f) for f in ("mg.hip", "mg_march.h", "march_box.h")]
 
 
 # kernel classes with a committed counter summary: profiles/<prefix>_<workload>_hbm_traffic.md

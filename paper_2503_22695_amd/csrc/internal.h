@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "hipib.h"
+#include "march_box.h"
 
 namespace hipib {
 
@@ -56,12 +57,6 @@ struct Level {
     void* x = nullptr;     // [3][n3] packed, l >= 1, element type of the V-cycle
     void* b = nullptr;
     void* x2 = nullptr;    // [3][n3] red cells of x after pre-smoothing (levels run as fused passes)
-};
-
-// Box of a fused smoothing pass: a workgroup owns XO packed columns x JO rows x ZO
-// planes; W = XO + 2 HX columns a row with the halo (HX = 0: the whole row)
-struct MarchBox {
-    int W, XO, HX, JO, ZO, ntx, nty, ntz, threads, lds;
 };
 
 struct StepRecord {

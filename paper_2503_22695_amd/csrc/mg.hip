@@ -2031,46 +2031,6 @@ bool marched(const hipib_ctx* ctx, int n) {
     return n % 8 == 0 && n >= 24 && ctx->cfg.mg_pre == 2 && ctx->cfg.mg_post == 2;
 }
 
-// Box of a fused pass.  A step of one workgroup takes about 0.05 us and 0.62 us
-// per 1024 resident threads (FP64, measured over boxes of 448 to 1024 threads on
-// 64^3 and 128^3: LDS accesses bound it; half of that in FP32), whatever part of
-// the threads is halo.  The box taken has the least rounds x steps x step time:
-// large ones repeat less halo, small ones fill the 256 CUs (128^3, one
-// component, down half: 32 x 16 x 8 19.7 us, 32 x 8 x 8 27.1, 32 x 16 x 16 24.5).
-// 1 + 4 / XO stands for the cache lines of a row that are only partly used
-// (192^3, three components, up half with the norm: 16 x 28 x 48 174 us,
-// 24 x 20 x 48 157; 256^3, down half from an iterate: 32 x 14 x 64 332,
-// 16 x 32 x 64 305).
-MarchBox march_box(int n, int ncomp, int halo, int halo_x, int extra, int slots, int esz) {
-    const int H = n / 2;
-    MarchBox best{};
-    double tbest = 0.0;
-    const int resident = esz == 8 ? 1024 : 2048;   // threads per CU with the registers of a pass
-    for (int XO : {H, 16, 24, 32, 48, 64}) {
-        if (XO > H || XO > 64) continue;
-        const int HX = XO == H ? 0 : halo_x, W = XO + 2 * HX;
-        for (int JO = 4; JO <= 32 && JO <= n; JO += 2) {
-            const int threads = (W * (JO + 2 * halo) + 63) / 64 * 64;
-            const int lds = slots * threads * esz;
-            if (threads > kMarchThreads || lds > 160 * 1024) break;
-            for (int ZO : {4, 8, 12, 16, 24, 32, 48, 64}) {
-                if (ZO > n) break;
-                const int ntx = (H + XO - 1) / XO, nty = (n + JO - 1) / JO, ntz = (n + ZO - 1) / ZO;
-                const int per_cu = (ntx * nty * ntz * ncomp + 255) / 256;
-                const int fit = std::min(resident / threads, 160 * 1024 / lds), r = std::min(per_cu, fit);
-                const int steps = (ZO + 2 * halo + extra + 3) / 4 * 4;
-                const double t = (double)((per_cu + r - 1) / r) * steps * (0.05 + 0.62 * esz / 8 * threads * r / 1024.0) *
-                                 (1.0 + 4.0 / XO);
-                if (best.XO == 0 || t < tbest) {
-                    tbest = t;
-                    best = MarchBox{W, XO, HX, JO, ZO, ntx, nty, ntz, threads, lds};
-                }
-            }
-        }
-    }
-    return best;
-}
-
 // The box of a fused pass, kept in the context: boxes depend on the level, the
 // components and the pass only.
 template <int SRC, int NS, int RES, typename T>

@@ -33,18 +33,6 @@
 namespace hipib {
 namespace {
 
-enum MarchSource {
-    MARCH_ZERO = 0,    // from a zero guess: the red half-sweep x = b / diag
-    MARCH_GUESS = 1,   // from the black cells of x (over-relaxed: and the red ones)
-    MARCH_CORRECT = 2  // from the red cells of x plus the prolongated coarse correction
-};
-enum MarchResult {
-    MARCH_X = 0,         // both colours of the smoothed x
-    MARCH_RESTRICT = 1,  // its red cells and the restricted residual
-    MARCH_DOTS = 2,      // both colours, and the partial sums of r.z and z.q
-    MARCH_NORM = 3       // both colours, and the partial sums of ||b - A x||^2
-};
-
 template <typename T>
 struct MarchArgs {
     const T* x;       // guess, or the pre-smoothed x (red cells read)
@@ -66,7 +54,7 @@ struct MarchArgs {
     int64_t pstride;
 };
 
-// (arguments of their own: 64 B more cost each launch of the other passes 0.5 us)
+// (arguments of their own: 56 B more cost each launch of the other passes 0.5 us)
 template <typename T>
 struct MarchCgArgs : MarchArgs<T> {
     // CG: b is formed here as r = rold - alpha qd (mixed mode: r / ||b||, kept in b32),
@@ -82,29 +70,6 @@ struct MarchCgArgs : MarchArgs<T> {
 };
 
 constexpr int kMarchAhead = 4;        // planes read ahead
-constexpr int kMarchThreads = 1024;   // threads of a workgroup at most: 128 registers each
-
-// steps beyond the box and its halo: the restriction's two
-constexpr int march_extra(int result) { return result == MARCH_RESTRICT ? 2 : 0; }
-// halo of the source: one cell per half-sweep, one for a residual and one for its
-// restriction
-constexpr int march_halo(int ns, int result) {
-    return result == MARCH_RESTRICT ? ns + 2 : result == MARCH_NORM ? ns + 1 : ns;
-}
-// planes before the box at which a pass starts: even where coarse planes go with it
-constexpr int march_lead(int src, int ns, int result) {
-    return src == MARCH_CORRECT ? (march_halo(ns, result) + 1) / 2 * 2 : march_halo(ns, result);
-}
-// the same in packed columns; a corrected cell also needs the next column's row value
-constexpr int march_halo_x(int src, int ns, int result) {
-    return (march_halo(ns, result) + 1) / 2 + (src == MARCH_CORRECT ? 1 : 0);
-}
-// LDS values per column: two planes of each stage that a later one reads
-// in-plane (the last one too where a residual follows), two of the interpolated
-// coarse rows, four of the restricted residuals and their x sums; odd, so that a wavefront's 8-byte accesses spread over all banks
-constexpr int march_slots(int src, int ns, int result) {
-    return 2 * (ns + (result == MARCH_RESTRICT ? 3 : result == MARCH_NORM ? 1 : 0) + (src == MARCH_CORRECT ? 1 : 0)) + 1;
-}
 
 // s_barrier with the LDS writes before it visible to the workgroup; global
 // memory is not waited for (no thread reads what another one of the launch
