@@ -164,3 +164,45 @@ def test_norm_of_a_converged_cycle(torch_dev, hp, n, sigma):
     cyc, start = plain_ctx(hp, n, dt=1.0 / sigma, mg_rtol=1e-6).mg_solve(hp.OP_HELMHOLTZ, bd, xd)
     assert cyc[0] == 0
     assert abs(last[0] / start[0] - 1.0) <= 0.15, (last[0], start[0])
+
+
+@pytest.mark.parametrize("op,ncomp,dt", [("poisson", 1, 1e-3), ("helmholtz", 3, 1e-3), ("helmholtz", 3, 2e-4)])
+def test_fused_cycles_256(torch_dev, hp, ref, op, ncomp, dt):
+    """The boxes of 256^3 (a pass beyond the last-level cache), as test_fused_cycles;
+    of three components the last one is compared."""
+    n = 256
+    say("fused cycles", n, op, ncomp, dt)
+    rng = np.random.default_rng(n)
+    b = rng.standard_normal((ncomp, n, n, n))
+    b -= b.mean(axis=(1, 2, 3), keepdims=True)
+    poisson = op == "poisson"
+    ctx = plain_ctx(hp, n, dt=dt, mg_fixed_cycles=2)
+    xd = to_dev(torch_dev, np.zeros_like(b))
+    _, rr = ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
+    fl = ref.fluid(n, dt=dt, fixed_cycles=2)
+    xr, _, rrr = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[-1])
+    assert_close("x", host(xd)[-1], xr, TOL)
+    assert abs(rr[-1] - rrr) <= 1e-6 * rrr + 1e-13, (rr, rrr)
+
+
+@pytest.mark.parametrize("n,op,ncomp,dt", [(48, "poisson", 1, 1e-3), (64, "poisson", 3, 1e-3), (128, "poisson", 1, 1e-3),
+                                           (192, "poisson", 1, 1e-3), (128, "helmholtz", 3, 5e-4),
+                                           (96, "helmholtz", 3, 1e-2), (128, "helmholtz", 1, 5e-3)])
+def test_fused_cycle_fp32(torch_dev, hp, ref, n, op, ncomp, dt):
+    """One FP32 cycle of the FP64 residual against the oracle's FP64 cycle (the same
+    one, the smoother being linear).  Some ten operations of four roundings a level
+    and five levels at 6e-8 each: 1.2e-5 of the correction, so 2e-5."""
+    say("fused cycle, FP32", n, op, ncomp, dt)
+    rng = np.random.default_rng(2000 + n)
+    b = rng.standard_normal((ncomp, n, n, n))
+    b -= b.mean(axis=(1, 2, 3), keepdims=True)
+    x0 = 1e-3 * rng.standard_normal(b.shape)
+    x0 -= x0.mean(axis=(1, 2, 3), keepdims=True)
+    poisson = op == "poisson"
+    ctx = plain_ctx(hp, n, dt=dt, mg_fixed_cycles=1, mg_krylov=0, precision=hp.MIXED)
+    xd = to_dev(torch_dev, x0)
+    ctx.mg_solve(hp.OP_POISSON if poisson else hp.OP_HELMHOLTZ, to_dev(torch_dev, b), xd)
+    fl = ref.fluid(n, dt=dt, fixed_cycles=1, krylov=0)
+    for d in range(ncomp):
+        xr, _, _ = ref.mg_solve(fl, 0.0 if poisson else 1.0 / dt, 1.0 if poisson else 0.01, poisson, b[d], x0[d])
+        assert_close(f"correction[{d}]", host(xd)[d] - x0[d], xr - x0[d], 2e-5)
