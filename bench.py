@@ -237,7 +237,7 @@ def kernel_classes(hipib):
         (H.TIMER_CG_DOTS, "k_march<double,up,dots>",
          "finest-level up half of the preconditioner, with r.z and z.q, 29 B/cell"),
         (H.TIMER_CG_DIR, "k_cg_dir<double>", "p, q = A z + beta q and p.q, 40 B/cell (56 B with the x step of the iteration before)"),
-        (H.TIMER_CG_UPDATE, "k_cg_update",
+        (H.TIMER_CG_UPDATE, "k_cg_close / k_cg_update",
          "alpha from the p.q partials, x, r updates, ||r||^2 and sum-x partials, 48 B/cell"),
         (H.TIMER_REDUCE, "k_finalize / k_cg_scalars", "single-workgroup reductions, 8 B per partial"),
         (H.TIMER_RHS, "k_rhs_build",

@@ -27,9 +27,11 @@
 namespace hipib {
 namespace {
 
-// work items (the list's length is not known to the host) share at most so many
-// workgroups: as many as run at once (8 to a CU); a grid of the list's capacity is
-// mostly workgroups without an item.
+// Work items share at most so many workgroups (a grid stride): the list's length is
+// not known to the host, and a grid of its capacity is mostly workgroups without an
+// item.  An empirical cap that matters little: with 8192, 2048 and 768, spreading
+// takes 33.9, 34.5 and 36.5 us at 128^3 and 89.7, 90.0 and 90.9 at 192^3,
+// interpolation 25.6 and 40.1 to 40.8 in all three.
 constexpr int64_t kTileBlocks = 2048;
 
 // ---------------------------------------------------------------------------

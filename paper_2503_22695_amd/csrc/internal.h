@@ -80,8 +80,6 @@ struct hipib_ctx {
     int L = 0;              // number of levels
     int small_start = 0;    // first level run by the single-workgroup kernel
     size_t small_lds = 0;   // its dynamic LDS bytes
-    // exact solve of the coarsest level (mg_coarse_sweeps = 0): the level's real
-    // Fourier basis Q [N][N] and eigenvalue factors s [N], FP64 and FP32 copies
     // set by a conjugate-gradient iteration around its preconditioner: r and q
     // for the dots fused into the finest level's last half-sweeps (parts: the
     // partials those wrote, 0 if none)
@@ -113,6 +111,8 @@ struct hipib_ctx {
     int64_t norm_sums = 0;
     int exact_level = 0;    // first level with at most 32 cells per side (the exact coarsest level)
     void* coarse_work = nullptr;   // its transform array (24^3 and 32^3), 3 components
+    // its exact solve (mg_coarse_sweeps = 0): the level's real Fourier basis Q [N][N],
+    // eigenvalue factors s [N] and Q transposed [N][N], FP64 and FP32 copies
     double* coarse_tab = nullptr;
     float* coarse_tab32 = nullptr;
     hipib::Level lv[hipib::kMaxLevels];

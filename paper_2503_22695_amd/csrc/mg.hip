@@ -2585,17 +2585,17 @@ hipib_status mg_remove_mean(hipib_ctx* ctx, double* v, int /*slot*/) {
     return HIPIB_OK;
 }
 
+// device address of the state's mean[] (no host access to the state)
+const double* state_mean(const hipib_ctx* ctx) {
+    return reinterpret_cast<const double*>(reinterpret_cast<const char*>(ctx->st) + offsetof(MGState, mean));
+}
+
 // The solve on packed arrays: xpk holds the initial guess, ctx->bpk the
 // right-hand side.  b_ready: the state was reset and holds ||b - mean(b)|| and
 // the mean of b (Poisson, component 0), which the initial residual pass then
 // subtracts from b.  A converged Poisson solve leaves the solution's mean in
 // the state for the caller to subtract (the null space of the periodic
 // Laplacian); *mean_ok says whether it is there.
-// device address of the state's mean[] (no host access to the state)
-const double* state_mean(const hipib_ctx* ctx) {
-    return reinterpret_cast<const double*>(reinterpret_cast<const char*>(ctx->st) + offsetof(MGState, mean));
-}
-
 hipib_status solve_packed(hipib_ctx* ctx, int op, int ncomp, double* xpk, bool b_ready, int32_t* cycles,
                           double* relres, bool* mean_ok) {
     const OpCoef oc = op_coef(ctx, op);
